@@ -25,6 +25,7 @@
 #include "device.hpp"
 #include "dm.hpp"
 #include "math_gate.hpp"
+#include "measure.hpp"
 #include "qsv_internal.hpp"
 #include "tileprog.hpp"
 
@@ -54,7 +55,8 @@ struct qsv_sim {
     // workspace for reductions
     void *d_ws = nullptr;
     size_t ws_bytes = 0;
-    double *d_small = nullptr;         // 16 doubles
+    double *d_small = nullptr;         // 64 doubles
+    unsigned char *h_res = nullptr;    // pinned, written by kernels: results the host waits for
     // op pool for tile passes: pinned host staging + device copy, two slots
     struct Slot {
         void *h = nullptr;
@@ -192,12 +194,26 @@ qsv_status invalid_state(qsv_sim *s) {
                 "qsv_set_state");
 }
 
+// Small results: device scratch, and pinned host memory that the last kernel
+// of a reduction writes itself (no copy to wait for).
+constexpr size_t kResultBytes = 4096;
+
+qsv_status ensure_small(qsv_sim *s) {
+    if (!s->d_small) QSV_HIP(s, hipMalloc((void **)&s->d_small, 64 * sizeof(double)));
+    return QSV_OK;
+}
+
+qsv_status ensure_result(qsv_sim *s) {
+    if (!s->h_res) QSV_HIP(s, hipHostMalloc((void **)&s->h_res, kResultBytes, hipHostMallocDefault));
+    return QSV_OK;
+}
+
 qsv_status materialize(qsv_sim *s) {
     if (s->invalid) return invalid_state(s);
     if (s->materialized) return QSV_OK;
     QSV_TRY(ensure_capacity(s, s->n));
     QSV_HIP(s, qsv::dev::fill_basis0(s->opt.dtype, s->d_state, s->dim(), s->stream));
-    if (!s->d_small) QSV_HIP(s, hipMalloc((void **)&s->d_small, 64 * sizeof(double)));
+    QSV_TRY(ensure_small(s));
     s->materialized = true;
     return QSV_OK;
 }
@@ -759,6 +775,7 @@ qsv_status qsv_destroy(qsv_sim *s) {
     if (s->d_ws) (void)hipFree(s->d_ws);
     if (s->d_alt) (void)hipFree(s->d_alt);
     if (s->d_small) (void)hipFree(s->d_small);
+    if (s->h_res) (void)hipHostFree(s->h_res);
     for (auto &sl : s->slot) {
         if (sl.h) (void)hipHostFree(sl.h);
         if (sl.d) (void)hipFree(sl.d);
@@ -1264,6 +1281,32 @@ qsv_status qsv_measure(qsv_sim *s, int32_t m, const int32_t *qubits, const doubl
         if (!(u[j] >= 0.0 && u[j] < 1.0)) return fail(s, QSV_EINVAL, "uniform outside [0,1)");
     QSV_TRY(do_flush(s));
     QSV_TRY(materialize(s));
+    if (m == 0) return sync(s);
+    // All qubits in one sequence of kernels; a state whose weights are not
+    // ordinary numbers is left as it was by them and goes qubit by qubit.
+    qsv::dev::MeasureArgs a{};
+    a.nq = s->n;
+    a.m = m;
+    for (int j = 0; j < m; ++j) {
+        a.pos[j] = (uint32_t)s->pos_of[qubits[j]];
+        a.u[j] = u[j];
+    }
+    QSV_TRY(ensure_ws(s, qsv::dev::measure_workspace_bytes()));
+    QSV_TRY(ensure_result(s));
+    auto *br = reinterpret_cast<qsv::dev::MeasureBranch *>(s->h_res);
+    br->status = 1;
+    int launches = 0;
+    const double bytes = 2.0 * s->dim() * s->elem();
+    const int tok = tbegin(s);
+    QSV_HIP(s, qsv::dev::measure(s->opt.dtype, s->d_state, a, s->d_ws, br, &launches, s->stream));
+    tend(s, tok, QSV_K_REDUCE, bytes);
+    QSV_TRY(sync(s));
+    s->stats.kernels += launches;
+    s->stats.alg_bytes += bytes;
+    if (br->status == 0) {
+        for (int j = 0; j < m; ++j) bits_out[j] = (int8_t)((br->val >> a.pos[j]) & 1);
+        return QSV_OK;
+    }
     for (int j = 0; j < m; ++j) {
         const int pos = s->pos_of[qubits[j]];
         double p0, p1;
@@ -1392,7 +1435,7 @@ qsv_status qsv_set_state(qsv_sim *s, const void *src, int32_t src_is_device) {
     s->queue.clear();
     s->invalid = false;
     QSV_TRY(ensure_capacity(s, s->n));
-    if (!s->d_small) QSV_HIP(s, hipMalloc((void **)&s->d_small, 64 * sizeof(double)));
+    QSV_TRY(ensure_small(s));
     QSV_HIP(s, hipMemcpyAsync(s->d_state, src, s->dim() * s->elem(),
                               src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                               s->stream));
@@ -2020,7 +2063,7 @@ extern "C" qsv_status qsv_adjoint_gradient(qsv_sim *s, const qsv_circuit *circ,
     }
     const uint64_t dim = 1ull << n;
     QSV_TRY(ensure_vectors(s, dim));
-    if (!s->d_small) QSV_HIP(s, hipMalloc((void **)&s->d_small, 64 * sizeof(double)));
+    QSV_TRY(ensure_small(s));
     void *psi = s->d_vec[0], *phi = s->d_vec[1];
     // partial sums per rotation: nb per workgroup-wave of the tiled sweep
     // (mode TILED), else per workgroup of the per-gate reverse kernels
