@@ -221,22 +221,6 @@ hipError_t reduced_dm(int dtype, const void *psi, int nq, int k, const int *pos,
                       double *out_dev, hipStream_t s);
 size_t reduced_dm_workspace_bytes();
 
-// Pauli sum.  Terms are grouped by x mask on the host; `grp_*` describe the
-// groups.  out_dev[0..1] = sum_t coeff_t <P_t> (re, im).
-struct PauliGroup {
-    uint64_t x;
-    int32_t first;        // first term index of the group
-    int32_t count;        // terms in the group
-};
-hipError_t pauli_expectation(int dtype, const void *psi, int nq, int ngroups,
-                             const PauliGroup *groups_host, const uint64_t *z_dev,
-                             const double *coef_dev, const int32_t *ny_dev, int nterms,
-                             double *ws, size_t ws_bytes, double *out_dev, hipStream_t s,
-                             const uint64_t *z_host = nullptr);   // z masks on the host (same
-                                                                  // order): enables the one-read
-                                                                  // tiled path
-size_t pauli_workspace_bytes(int nq, int ngroups, int nterms);
-
 // ---------------------------------------------------------------- adjoint
 // phi = H psi for a Pauli sum over bit positions (device arrays).
 hipError_t ham_apply(int dtype, const void *psi, void *phi, uint64_t dim, int nterms,

@@ -26,6 +26,7 @@
 #include "dm.hpp"
 #include "math_gate.hpp"
 #include "measure.hpp"
+#include "pauli.hpp"
 #include "qsv_internal.hpp"
 #include "tileprog.hpp"
 
@@ -1188,53 +1189,29 @@ qsv_status qsv_get_probabilities(qsv_sim *s, double *out, int32_t out_is_device)
     return sync(s);
 }
 
-// Pauli sum over bit positions (shared by the ABI call and the adjoint).
-static qsv_status expectation_positions(qsv_sim *s, const void *psi, int nq, int nterms,
-                                        const uint64_t *x, const uint64_t *z, const double *c,
-                                        double *re_out, double *im_out) {
-    std::vector<int> order(nterms);
-    for (int t = 0; t < nterms; ++t) order[t] = t;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return x[a] < x[b]; });
-    std::vector<uint64_t> zs(nterms + 1);
-    std::vector<double> cs(nterms + 1);
-    std::vector<int32_t> ny(nterms + 1);
-    std::vector<qsv::dev::PauliGroup> groups;
-    for (int i = 0; i < nterms; ++i) {
-        const int t = order[i];
-        zs[i] = z[t];
-        cs[i] = c[t];
-        ny[i] = popc(x[t] & z[t]);
-        if (groups.empty() || groups.back().x != x[t]) groups.push_back({x[t], i, 0});
-        groups.back().count += 1;
-    }
-    int nchunks = 0;
-    for (auto &g : groups) nchunks += (g.count + 7) / 8;
-    const size_t meta = ((nterms + 1) * (8 + 8 + 4) + 255) & ~size_t(255);
-    const size_t need = qsv::dev::pauli_workspace_bytes(nq, nchunks, nterms) + meta + 4096;
-    QSV_TRY(ensure_ws(s, need));
-    unsigned char *w = (unsigned char *)s->d_ws;
-    uint64_t *dz = (uint64_t *)w;
-    double *dc = (double *)(w + 8 * (nterms + 1));
-    int32_t *dny = (int32_t *)(w + 16 * (nterms + 1));
-    std::vector<unsigned char> hostmeta(meta, 0);
-    std::memcpy(hostmeta.data(), zs.data(), 8 * (nterms + 1));
-    std::memcpy(hostmeta.data() + 8 * (nterms + 1), cs.data(), 8 * (nterms + 1));
-    std::memcpy(hostmeta.data() + 16 * (nterms + 1), ny.data(), 4 * (nterms + 1));
-    QSV_HIP(s, hipMemcpyAsync(w, hostmeta.data(), meta, hipMemcpyHostToDevice, s->stream));
-    QSV_HIP(s, hipStreamSynchronize(s->stream));
-    double *ws = (double *)(w + meta);
+// Pauli sum over bit positions.
+static qsv_status expectation_positions(qsv_sim *s, int nterms, const uint64_t *x,
+                                        const uint64_t *z, const double *c, double *out) {
+    *out = 0.0;
+    if (nterms == 0) return sync(s);
+    qsv::dev::PauliPlan p;
+    qsv::dev::pauli_plan(s->n, nterms, x, z, c, p);
+    std::vector<unsigned char> blob(qsv::dev::pauli_blob_bytes(p));
+    qsv::dev::pauli_blob(p, blob.data());
+    void *dblob = nullptr;
+    QSV_TRY(stage(s, blob.data(), blob.size(), &dblob));
+    QSV_TRY(ensure_ws(s, p.partials() * sizeof(double)));
+    QSV_TRY(ensure_result(s));
+    double *res = reinterpret_cast<double *>(s->h_res);
+    const double bytes = (double)(p.sets.size() + p.wide.size()) * (double)s->dim() * s->elem();
     const int tok = tbegin(s);
-    QSV_HIP(s, qsv::dev::pauli_expectation(s->opt.dtype, psi, nq, (int)groups.size(), groups.data(),
-                                           dz, dc, dny, nterms, ws, s->ws_bytes - meta,
-                                           s->d_small, s->stream, zs.data()));
-    tend(s, tok, QSV_K_REDUCE, (double)nchunks * (double)(1ull << nq) * s->elem());
-    double h[2];
-    QSV_HIP(s, hipMemcpyAsync(h, s->d_small, sizeof(h), hipMemcpyDeviceToHost, s->stream));
+    QSV_HIP(s, qsv::dev::pauli_sum(s->opt.dtype, s->d_state, s->n, p, dblob, (double *)s->d_ws, res,
+                                   s->stream));
+    tend(s, tok, QSV_K_REDUCE, bytes);
     QSV_TRY(sync(s));
-    s->stats.kernels += 2;
-    s->stats.alg_bytes += (double)nchunks * (double)(1ull << nq) * s->elem();
-    *re_out = h[0];
-    if (im_out) *im_out = h[1];
+    s->stats.kernels += 1 + (p.sets.empty() ? 0 : 1) + (p.wide.empty() ? 0 : 1);
+    s->stats.alg_bytes += bytes;
+    *out = *res;
     return QSV_OK;
 }
 
@@ -1260,8 +1237,22 @@ qsv_status qsv_get_expectation_complex(qsv_sim *s, int32_t nterms, const uint64_
     }
     QSV_TRY(do_flush(s));
     QSV_TRY(materialize(s));
-    return expectation_positions(s, s->d_state, s->n, nterms, x.data(), z.data(), coeff, re_out,
-                                 im_out);
+    // The strings' coefficients go into one running sum; one that is not finite
+    // multiplies its string's value instead.
+    std::vector<double> c(coeff, coeff + nterms);
+    double odd = 0.0, one = 1.0;
+    for (int t = 0; t < nterms; ++t)
+        if (!std::isfinite(c[t])) {
+            double v = 0.0;
+            QSV_TRY(expectation_positions(s, 1, &x[t], &z[t], &one, &v));
+            odd += c[t] * v;
+            c[t] = 0.0;
+        }
+    QSV_TRY(expectation_positions(s, nterms, x.data(), z.data(), c.data(), re_out));
+    *re_out += odd;
+    // each pair's imaginary parts cancel; a state that is not finite shows
+    *im_out = *re_out - *re_out;
+    return QSV_OK;
 }
 
 qsv_status qsv_get_expectation(qsv_sim *s, int32_t nterms, const uint64_t *xmask,
