@@ -10,7 +10,11 @@
 // coefficient goes in with the thread's sign, so that one running sum serves
 // every string.  The next tile's amplitudes are on their way meanwhile.  With
 // 12 bits of tile a sum of 200 random strings of weight <= 4 on 25 qubits (111
-// X masks) reads the state 8 times.
+// X masks) reads the state 8 times: 1.73 ms in complex128, 2.5 TB/s, of which
+// the reads alone would take 0.7; the rest is the latency of 14 groups a tile
+// (21 vector and about 50 scalar instructions each) at four waves per SIMD.  As
+// one sweep per X mask it took 11.8 ms.  8 strings on 30 qubits: 2 reads, 5.7 ms
+// (6.0 TB/s), against 24.7.
 // k_pauli_wide: the strings that fit in no tile, one sweep per X mask.
 #include <hip/hip_runtime.h>
 
@@ -44,25 +48,21 @@ __device__ __forceinline__ double sign_flip(double v, uint32_t s) {    // s = 0 
     return __hiloint2double(__double2hiint(v) ^ (int)(s << 31), __double2loint(v));
 }
 
-// A group's terms over the products q[i] of the registers i with bit HB clear
-// (HB < 0: all).
+// A string over the products q[i] of the registers i with bit HB clear (HB < 0:
+// all).
 template <int NR, int HB>
-__device__ __forceinline__ void pauli_terms(double &acc, const double *q, const PauliXGroup &g,
-                                            const PauliTerm *__restrict__ terms, uint64_t base,
-                                            uint32_t tid) {
-    for (int t = g.term0; t < g.term0 + g.terms; ++t) {
-        const PauliTerm &pt = terms[t];
-        const uint32_t sreg = pt.sreg;
-        double local = 0.0;
+__device__ __forceinline__ void pauli_term(double &acc, const double *q, const PauliTerm &pt,
+                                           uint64_t base, uint32_t tid) {
+    const uint32_t sreg = pt.sreg;
+    double local = 0.0;
 #pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            if (HB >= 0 && ((i >> (HB < 0 ? 0 : HB)) & 1)) continue;
-            const double sg = __hiloint2double((int)(0x3ff00000u | (((sreg >> i) & 1u) << 31)), 0);
-            local = __builtin_fma(q[i], sg, local);
-        }
-        const uint32_t st = (uint32_t)(__popcll(base & pt.zo) + __popc(tid & pt.zthr)) & 1u;
-        acc = __builtin_fma(local, sign_flip(pt.c, st), acc);
+    for (int i = 0; i < NR; ++i) {
+        if (HB >= 0 && ((i >> (HB < 0 ? 0 : HB)) & 1)) continue;
+        const double sg = __hiloint2double((int)(0x3ff00000u | (((sreg >> i) & 1u) << 31)), 0);
+        local = __builtin_fma(q[i], sg, local);
     }
+    const uint32_t st = (uint32_t)(__popcll(base & pt.zo) + __popc(tid & pt.zthr)) & 1u;
+    acc = __builtin_fma(local, sign_flip(pt.c, st), acc);
 }
 
 // X: the X mask over the register bits.
@@ -91,7 +91,8 @@ __device__ __forceinline__ void pauli_group(double &acc, const typename VP<R>::T
             if (HB < 0 || !((i >> (HB < 0 ? 0 : HB)) & 1))
                 q[i] = __builtin_fma((double)b[i].x, (double)amp[i].x, (double)b[i].y * (double)amp[i].y);
     }
-    pauli_terms<NR, HB>(acc, q, g, terms, base, tid);
+    pauli_term<NR, HB>(acc, q, g.first, base, tid);
+    for (int t = g.term0; t < g.term0 + g.terms; ++t) pauli_term<NR, HB>(acc, q, terms[t], base, tid);
 }
 
 template <typename T, int RB>
@@ -157,8 +158,11 @@ __global__ __launch_bounds__(kPT, 4) void k_pauli_tiles(
             base = base_of(t);
             pauli_load<T, RB>(next, psi, base | thr, reg, pad_reg, on);
         }
-        for (int gi = st.group0; gi < st.group0 + st.groups; ++gi) {
-            const PauliXGroup &g = groups[gi];
+        // the next group's line is on its way while a group is worked on
+        PauliXGroup ahead = groups[st.group0];
+        for (int gi = 0; gi < st.groups; ++gi) {
+            const PauliXGroup g = ahead;
+            ahead = groups[st.group0 + (gi + 1 < st.groups ? gi + 1 : gi)];
 #define QSV_PX(X)                                                                        \
     case X:                                                                              \
         if constexpr (X < NR) pauli_group<R, RB, (X < NR ? X : 0)>(acc, amp, tile, g, terms, here, tid); \
@@ -228,10 +232,10 @@ static hipError_t pauli_sum_t(const void *psi, int nq, const PauliPlan &p, const
     using T = typename VP<R>::T;
     constexpr int RB = kPauliRegBits, m = kPauliTileBits;
     const unsigned char *b = static_cast<const unsigned char *>(blob);
-    const auto *wide = reinterpret_cast<const PauliWideGroup *>(b);
-    const auto *sets = reinterpret_cast<const PauliSet *>(b + p.wide.size() * sizeof(PauliWideGroup));
-    const auto *groups = reinterpret_cast<const PauliXGroup *>(sets + p.sets.size());
-    const auto *terms = reinterpret_cast<const PauliTerm *>(groups + p.groups.size());
+    const auto *groups = reinterpret_cast<const PauliXGroup *>(b);
+    const auto *wide = reinterpret_cast<const PauliWideGroup *>(groups + p.groups.size());
+    const auto *sets = reinterpret_cast<const PauliSet *>(wide + p.wide.size());
+    const auto *terms = reinterpret_cast<const PauliTerm *>(sets + p.sets.size());
     double *at = ws;
     // rows of the grid go in the y dimension, at most kRows of them at once
     constexpr size_t kRows = 32768;

@@ -32,13 +32,17 @@ struct PauliTerm {
     uint32_t zthr;
     uint32_t sreg;
 };
-// Strings with one X mask, over the tile's bits.
+// Strings with one X mask, over the tile's bits.  The first string is held in
+// place: most groups have no other, and one burst of scalar loads (a 64-byte
+// line) then brings all that a group needs.
 struct PauliXGroup {
+    PauliTerm first;
     uint32_t xthr, xreg;
     int32_t odd;            // n_Y odd: Im, else Re
-    int32_t term0, terms;
-    int32_t pad[3];
+    int32_t term0, terms;   // the others
+    int32_t pad[5];
 };
+static_assert(sizeof(PauliXGroup) == 64, "a group is one line");
 // A tile shape (positions of the local bits: 9 thread bits, then the register
 // bits) and the groups whose X letters it holds; one row of the grid.
 struct PauliSet {

@@ -123,7 +123,7 @@ void pauli_plan(int nq, int nterms, const uint64_t *x, const uint64_t *z,
             g.odd = key.second;
             g.term0 = (int32_t)p.terms.size();
             const std::vector<int> &ts = by[key];
-            g.terms = (int32_t)ts.size();
+            g.terms = (int32_t)ts.size() - 1;
             for (int t : ts) {
                 PauliTerm q{};
                 const uint32_t zl = local(z[t]);
@@ -132,7 +132,8 @@ void pauli_plan(int nq, int nterms, const uint64_t *x, const uint64_t *z,
                 q.zthr = zl & tmask;
                 for (int i = 0; i < nr; ++i)
                     if (__builtin_popcount((uint32_t)i & (zl >> kPauliThreadBits)) & 1) q.sreg |= 1u << i;
-                p.terms.push_back(q);
+                if (t == ts.front()) g.first = q;
+                else p.terms.push_back(q);
             }
             p.groups.push_back(g);
         }
@@ -176,9 +177,9 @@ void pauli_blob(const PauliPlan &p, unsigned char *out) {
         if (n) std::memcpy(out, d, n);
         out += n;
     };
+    put(p.groups.data(), p.groups.size() * sizeof(PauliXGroup));    // on their lines
     put(p.wide.data(), p.wide.size() * sizeof(PauliWideGroup));
     put(p.sets.data(), p.sets.size() * sizeof(PauliSet));
-    put(p.groups.data(), p.groups.size() * sizeof(PauliXGroup));
     put(p.terms.data(), p.terms.size() * sizeof(PauliTerm));
 }
 
