@@ -332,10 +332,11 @@ hipError_t batch_launch(int dtype, const BatchLaunch &L, hipStream_t s);
 int batch_occupancy(int dtype, int mb, int mfma_k);   // resident workgroups per CU
 int batch_pass_occupancy(int dtype, int mb, int mfma_k);
 
-// Sampling: out_dev[shots] indices.
+// Sampling: out[shots] indices for the uniforms u[shots], both in device memory
+// or in host memory that the device reads and writes.
 size_t sample_workspace_bytes(int nq);
-hipError_t sample(int dtype, const void *psi, int nq, int shots, const double *u_dev,
-                  double *ws, uint64_t *out_dev, hipStream_t s);
+hipError_t sample(int dtype, const void *psi, int nq, int shots, const double *u, void *ws,
+                  uint64_t *out, hipStream_t s);
 
 }  // namespace dev
 }  // namespace qsv

@@ -1,5 +1,5 @@
 // Reductions and whole-state operations: probabilities, masked probability
-// sums, sampling, collapse after measurement,
+// sums, collapse after measurement,
 // qubit allocation (zero extension) and deallocation (compaction).  Every sum
 // is accumulated in double precision whatever the state's dtype.
 #include <hip/hip_runtime.h>
@@ -54,17 +54,35 @@ static unsigned red_grid(uint64_t work) {
 }
 
 // ------------------------------------------------------------ probability
+// A workgroup takes runs of 2048 amplitudes, eight loads of a thread in flight:
+// bound by HBM, 16 GiB in 2.80 ms (6.1 TB/s; one load at a time from a grid-wide
+// stride 3.14, eight of them 3.09).
 template <typename R>
 __global__ __launch_bounds__(kRedThreads) void k_prob_masked(const typename V2r<R>::T *psi,
                                                              uint64_t ngroups, IndexArgs ia,
                                                              double *partial) {
+    constexpr int U = 8;
     __shared__ double sh[16];
     double acc = 0.0;
-    for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < ngroups;
-         g += (uint64_t)gridDim.x * blockDim.x) {
-        const auto a = psi[expand_idx(g, ia)];
-        const double re = a.x, im = a.y;
-        acc += re * re + im * im;
+    if (ngroups >= U * kRedThreads) {      // a power of two: whole runs
+        for (uint64_t r = blockIdx.x; r < ngroups / (U * kRedThreads); r += gridDim.x) {
+            const uint64_t g = r * (U * kRedThreads) + threadIdx.x;
+            typename V2r<R>::T v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = psi[expand_idx(g + u * kRedThreads, ia)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const double re = v[u].x, im = v[u].y;
+                acc += re * re + im * im;
+            }
+        }
+    } else {
+        for (uint64_t g = (uint64_t)blockIdx.x * kRedThreads + threadIdx.x; g < ngroups;
+             g += (uint64_t)gridDim.x * kRedThreads) {
+            const auto a = psi[expand_idx(g, ia)];
+            const double re = a.x, im = a.y;
+            acc += re * re + im * im;
+        }
     }
     acc = block_sum(acc, sh);
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
@@ -273,188 +291,6 @@ hipError_t probs(int dtype, const void *psi, uint64_t dim, double *out_dev, hipS
     else
         hipLaunchKernelGGL(k_probs<float>, dim3(g), dim3(256), 0, s, (const float2 *)psi, dim,
                            out_dev);
-    return hipGetLastError();
-}
-
-// --------------------------------------------------------------- sampling
-// Blocks of 2^kSampleBits amplitudes: block sums and last nonzero index, an
-// exclusive scan of the block sums, then one workgroup per shot resolves the
-// index inside its block.
-constexpr int kSampleBits = 12;
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_block_sums(const typename V2r<R>::T *psi, int bbits,
-                                                    double *bsum, int64_t *blast) {
-    __shared__ double sh[16];
-    __shared__ int64_t shl[4];
-    const uint64_t b0 = (uint64_t)blockIdx.x << bbits;
-    const int per = (1 << bbits) / 256 > 0 ? (1 << bbits) / 256 : 1;
-    double acc = 0.0;
-    int64_t last = -1;
-    // lanes read consecutive amplitudes (coalesced); the order of the sum
-    // need not match the in-block scan of k_sample, which settles a draw
-    // that lands past its block's rounded end on the block's last nonzero
-    for (int j = 0; j < per; ++j) {
-        const uint32_t l = (uint32_t)j * 256u + threadIdx.x;
-        if (l >= (1u << bbits)) break;
-        const auto a = psi[b0 + l];
-        const double p = (double)a.x * a.x + (double)a.y * a.y;
-        acc += p;
-        if (p > 0.0) last = (int64_t)(b0 + l);
-    }
-    acc = block_sum(acc, sh);
-    for (int o = 32; o > 0; o >>= 1) {
-        const int64_t other = __shfl_down(last, o, 64);
-        last = other > last ? other : last;
-    }
-    if ((threadIdx.x & 63) == 0) shl[threadIdx.x >> 6] = last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t m = shl[0];
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = shl[w] > m ? shl[w] : m;
-        bsum[blockIdx.x] = acc;
-        blast[blockIdx.x] = m;
-    }
-}
-
-// Exclusive scan of nb block sums into prefix[0..nb] (prefix[nb] = total),
-// and the largest nonzero index into *glast.  One workgroup of 1024 threads.
-__global__ __launch_bounds__(1024) void k_scan(const double *bsum, const int64_t *blast,
-                                               uint64_t nb, double *prefix, int64_t *glast) {
-    __shared__ double sh[1024];
-    __shared__ int64_t shl[1024];
-    const uint64_t per = (nb + 1023) / 1024;
-    const uint64_t lo = threadIdx.x * per;
-    const uint64_t hi = lo + per < nb ? lo + per : nb;
-    double s = 0.0;
-    int64_t last = -1;
-    for (uint64_t i = lo; i < hi; ++i) {
-        s += bsum[i];
-        last = blast[i] > last ? blast[i] : last;
-    }
-    sh[threadIdx.x] = s;
-    shl[threadIdx.x] = last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double run = 0.0;
-        int64_t m = -1;
-        for (int t = 0; t < 1024; ++t) {
-            const double v = sh[t];
-            sh[t] = run;
-            run += v;
-            m = shl[t] > m ? shl[t] : m;
-        }
-        prefix[nb] = run;
-        *glast = m;
-    }
-    __syncthreads();
-    double run = sh[threadIdx.x];
-    for (uint64_t i = lo; i < hi; ++i) {
-        prefix[i] = run;
-        run += bsum[i];
-    }
-}
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_sample(const typename V2r<R>::T *psi, int bbits,
-                                                uint64_t nb, const double *prefix,
-                                                const int64_t *glast, const double *u,
-                                                uint64_t *out) {
-    __shared__ double sh[256];
-    __shared__ uint64_t blk_s;
-    __shared__ unsigned long long found;
-    __shared__ long long lastnz;
-    const double total = prefix[nb];
-    const double r = u[blockIdx.x] * total;
-    if (threadIdx.x == 0) {
-        // first block whose end prefix exceeds r
-        uint64_t lo = 0, hi = nb;
-        while (lo < hi) {
-            const uint64_t mid = lo + (hi - lo) / 2;
-            if (prefix[mid + 1] > r) hi = mid;
-            else lo = mid + 1;
-        }
-        blk_s = lo;
-        found = ~0ull;
-        lastnz = -1;
-    }
-    __syncthreads();
-    const uint64_t blk = blk_s;
-    if (blk >= nb) {
-        if (threadIdx.x == 0) out[blockIdx.x] = (uint64_t)(*glast < 0 ? 0 : *glast);
-        return;
-    }
-    const int bsize = 1 << bbits;
-    const int per = bsize / 256 > 0 ? bsize / 256 : 1;
-    const uint64_t b0 = blk << bbits;
-    double seg = 0.0;
-    for (int j = 0; j < per; ++j) {
-        const int l = threadIdx.x * per + j;
-        if (l >= bsize) break;
-        const auto a = psi[b0 + l];
-        seg += (double)a.x * a.x + (double)a.y * a.y;
-    }
-    sh[threadIdx.x] = seg;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double run = 0.0;
-        for (int t = 0; t < 256; ++t) {
-            const double v = sh[t];
-            sh[t] = run;
-            run += v;
-        }
-    }
-    __syncthreads();
-    double c = prefix[blk] + sh[threadIdx.x];
-    for (int j = 0; j < per; ++j) {
-        const int l = threadIdx.x * per + j;
-        if (l >= bsize) break;
-        const auto a = psi[b0 + l];
-        const double p = (double)a.x * a.x + (double)a.y * a.y;
-        c += p;
-        if (p > 0.0) atomicMax(&lastnz, (long long)(b0 + l));
-        if (c > r) {
-            atomicMin(&found, (unsigned long long)(b0 + l));
-            break;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t res = found;
-        if (res == ~0ull) res = lastnz >= 0 ? (uint64_t)lastnz : (uint64_t)(*glast < 0 ? 0 : *glast);
-        out[blockIdx.x] = res;
-    }
-}
-
-size_t sample_workspace_bytes(int nq) {
-    const int bb = nq < kSampleBits ? nq : kSampleBits;
-    const uint64_t nb = 1ull << (nq - bb);
-    return sizeof(double) * (2 * nb + 2) + sizeof(int64_t) * (nb + 2);
-}
-
-hipError_t sample(int dtype, const void *psi, int nq, int shots, const double *u_dev,
-                  double *ws, uint64_t *out_dev, hipStream_t s) {
-    const int bb = nq < kSampleBits ? nq : kSampleBits;
-    const uint64_t nb = 1ull << (nq - bb);
-    double *bsum = ws;
-    double *prefix = ws + nb;
-    int64_t *blast = (int64_t *)(prefix + nb + 2);
-    int64_t *glast = blast + nb;
-    if (dtype == 0)
-        hipLaunchKernelGGL(k_block_sums<double>, dim3((unsigned)nb), dim3(256), 0, s,
-                           (const double2 *)psi, bb, bsum, blast);
-    else
-        hipLaunchKernelGGL(k_block_sums<float>, dim3((unsigned)nb), dim3(256), 0, s,
-                           (const float2 *)psi, bb, bsum, blast);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, bsum, blast, nb, prefix, glast);
-    if (shots > 0) {
-        if (dtype == 0)
-            hipLaunchKernelGGL(k_sample<double>, dim3(shots), dim3(256), 0, s,
-                               (const double2 *)psi, bb, nb, prefix, glast, u_dev, out_dev);
-        else
-            hipLaunchKernelGGL(k_sample<float>, dim3(shots), dim3(256), 0, s,
-                               (const float2 *)psi, bb, nb, prefix, glast, u_dev, out_dev);
-    }
     return hipGetLastError();
 }
 

@@ -56,8 +56,8 @@ struct qsv_sim {
     // workspace for reductions
     void *d_ws = nullptr;
     size_t ws_bytes = 0;
-    double *d_small = nullptr;         // 64 doubles
-    unsigned char *h_res = nullptr;    // pinned, written by kernels: results the host waits for
+    unsigned char *h_res = nullptr;    // pinned: small inputs and results of the reductions, read
+                                       // and written by their kernels directly
     // op pool for tile passes: pinned host staging + device copy, two slots
     struct Slot {
         void *h = nullptr;
@@ -195,26 +195,25 @@ qsv_status invalid_state(qsv_sim *s) {
                 "qsv_set_state");
 }
 
-// Small results: device scratch, and pinned host memory that the last kernel
-// of a reduction writes itself (no copy to wait for).
-constexpr size_t kResultBytes = 4096;
-
-qsv_status ensure_small(qsv_sim *s) {
-    if (!s->d_small) QSV_HIP(s, hipMalloc((void **)&s->d_small, 64 * sizeof(double)));
-    return QSV_OK;
-}
+// Pinned memory in which a reduction's last kernel leaves its result, so that
+// the host waits for that kernel and for no copy; sampling keeps its uniforms
+// and indices there too, up to kDirectShots of them.
+constexpr size_t kDirectShots = 4096;
+constexpr size_t kResultBytes = 16 * kDirectShots;
 
 qsv_status ensure_result(qsv_sim *s) {
     if (!s->h_res) QSV_HIP(s, hipHostMalloc((void **)&s->h_res, kResultBytes, hipHostMallocDefault));
     return QSV_OK;
 }
 
+double *result(qsv_sim *s) { return reinterpret_cast<double *>(s->h_res); }
+
 qsv_status materialize(qsv_sim *s) {
     if (s->invalid) return invalid_state(s);
     if (s->materialized) return QSV_OK;
     QSV_TRY(ensure_capacity(s, s->n));
     QSV_HIP(s, qsv::dev::fill_basis0(s->opt.dtype, s->d_state, s->dim(), s->stream));
-    QSV_TRY(ensure_small(s));
+    QSV_TRY(ensure_result(s));
     s->materialized = true;
     return QSV_OK;
 }
@@ -645,13 +644,11 @@ qsv_status prob_split_host(qsv_sim *s, int pos, double *p0, double *p1) {
     QSV_TRY(ensure_ws(s, qsv::dev::reduce_workspace_bytes(s->n)));
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::prob_split(s->opt.dtype, s->d_state, s->n, pos, (double *)s->d_ws,
-                                    s->d_small, s->stream));
+                                    result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)s->dim() * s->elem());
-    double h[2];
-    QSV_HIP(s, hipMemcpyAsync(h, s->d_small, sizeof(h), hipMemcpyDeviceToHost, s->stream));
     QSV_TRY(sync(s));
-    *p0 = h[0];
-    *p1 = h[1];
+    *p0 = result(s)[0];
+    *p1 = result(s)[1];
     s->stats.kernels += 2;
     s->stats.alg_bytes += (double)s->dim() * s->elem();
     return QSV_OK;
@@ -775,7 +772,6 @@ qsv_status qsv_destroy(qsv_sim *s) {
     if (s->owns_state && s->d_state) (void)hipFree(s->d_state);
     if (s->d_ws) (void)hipFree(s->d_ws);
     if (s->d_alt) (void)hipFree(s->d_alt);
-    if (s->d_small) (void)hipFree(s->d_small);
     if (s->h_res) (void)hipHostFree(s->h_res);
     for (auto &sl : s->slot) {
         if (sl.h) (void)hipHostFree(sl.h);
@@ -1135,12 +1131,13 @@ qsv_status qsv_get_probability(qsv_sim *s, int32_t m, const int32_t *qubits, con
     index_args(mask, ones, ia);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::prob_masked(s->opt.dtype, s->d_state, 1ull << (s->n - m), ia,
-                                     (double *)s->d_ws, s->d_small, s->stream));
+                                     (double *)s->d_ws, result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)(1ull << (s->n - m)) * s->elem());
-    QSV_HIP(s, hipMemcpyAsync(out, s->d_small, sizeof(double), hipMemcpyDeviceToHost, s->stream));
     s->stats.kernels += 2;
     s->stats.alg_bytes += (double)(1ull << (s->n - m)) * s->elem();
-    return sync(s);
+    QSV_TRY(sync(s));
+    *out = *result(s);
+    return QSV_OK;
 }
 
 qsv_status qsv_get_probability_noalloc(const void *state, int32_t dtype, int32_t n, int32_t m,
@@ -1201,17 +1198,15 @@ static qsv_status expectation_positions(qsv_sim *s, int nterms, const uint64_t *
     void *dblob = nullptr;
     QSV_TRY(stage(s, blob.data(), blob.size(), &dblob));
     QSV_TRY(ensure_ws(s, p.partials() * sizeof(double)));
-    QSV_TRY(ensure_result(s));
-    double *res = reinterpret_cast<double *>(s->h_res);
     const double bytes = (double)(p.sets.size() + p.wide.size()) * (double)s->dim() * s->elem();
     const int tok = tbegin(s);
-    QSV_HIP(s, qsv::dev::pauli_sum(s->opt.dtype, s->d_state, s->n, p, dblob, (double *)s->d_ws, res,
-                                   s->stream));
+    QSV_HIP(s, qsv::dev::pauli_sum(s->opt.dtype, s->d_state, s->n, p, dblob, (double *)s->d_ws,
+                                   result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, bytes);
     QSV_TRY(sync(s));
     s->stats.kernels += 1 + (p.sets.empty() ? 0 : 1) + (p.wide.empty() ? 0 : 1);
     s->stats.alg_bytes += bytes;
-    *out = *res;
+    *out = *result(s);
     return QSV_OK;
 }
 
@@ -1283,7 +1278,6 @@ qsv_status qsv_measure(qsv_sim *s, int32_t m, const int32_t *qubits, const doubl
         a.u[j] = u[j];
     }
     QSV_TRY(ensure_ws(s, qsv::dev::measure_workspace_bytes()));
-    QSV_TRY(ensure_result(s));
     auto *br = reinterpret_cast<qsv::dev::MeasureBranch *>(s->h_res);
     br->status = 1;
     int launches = 0;
@@ -1332,14 +1326,12 @@ qsv_status qsv_apply_kraus_sampled(qsv_sim *s, int32_t nk, const double *kraus, 
     QSV_TRY(ensure_ws(s, qsv::dev::reduced_dm_workspace_bytes()));
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::reduced_dm(s->opt.dtype, s->d_state, s->n, k, pos, (double *)s->d_ws,
-                                    s->d_small, s->stream));
+                                    result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)s->dim() * s->elem());
-    double h[32];
-    QSV_HIP(s, hipMemcpyAsync(h, s->d_small, sizeof(double) * 2 * D * D, hipMemcpyDeviceToHost,
-                              s->stream));
     s->stats.kernels += 2;
     s->stats.alg_bytes += (double)s->dim() * s->elem();
     QSV_TRY(sync(s));
+    const double *h = result(s);
     std::vector<cd> rho((size_t)D * D);
     for (int e = 0; e < D * D; ++e) rho[e] = cd(h[2 * e], h[2 * e + 1]);
     // p_j = ||K_j psi||^2 = Tr(K_j rho K_j^dagger)
@@ -1392,21 +1384,24 @@ qsv_status qsv_sample(qsv_sim *s, int32_t shots, const double *u, uint64_t *out)
     QSV_TRY(do_flush(s));
     QSV_TRY(materialize(s));
     if (shots == 0) return QSV_OK;
-    const size_t wsb = qsv::dev::sample_workspace_bytes(s->n);
-    const size_t ub = ((size_t)shots * 8 + 255) & ~size_t(255);
-    QSV_TRY(ensure_ws(s, wsb + 2 * ub + 256));
+    const size_t wsb = (qsv::dev::sample_workspace_bytes(s->n) + 255) & ~size_t(255);
+    const size_t ub = (size_t)shots * 8;
+    const bool direct = (size_t)shots <= kDirectShots;
+    QSV_TRY(ensure_ws(s, wsb + (direct ? 0 : 2 * ub)));
     unsigned char *w = (unsigned char *)s->d_ws;
-    double *du = (double *)w;
-    uint64_t *dout = (uint64_t *)(w + ub);
-    double *dws = (double *)(w + 2 * ub);
-    QSV_HIP(s, hipMemcpyAsync(du, u, shots * sizeof(double), hipMemcpyHostToDevice, s->stream));
+    double *du = direct ? result(s) : (double *)(w + wsb);
+    uint64_t *dout = reinterpret_cast<uint64_t *>(du + shots);
+    if (direct) std::memcpy(du, u, ub);
+    else QSV_HIP(s, hipMemcpyAsync(du, u, ub, hipMemcpyHostToDevice, s->stream));
     const int tok = tbegin(s);
-    QSV_HIP(s, qsv::dev::sample(s->opt.dtype, s->d_state, s->n, shots, du, dws, dout, s->stream));
+    QSV_HIP(s, qsv::dev::sample(s->opt.dtype, s->d_state, s->n, shots, du, w, dout, s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)s->dim() * s->elem());
-    QSV_HIP(s, hipMemcpyAsync(out, dout, shots * sizeof(uint64_t), hipMemcpyDeviceToHost, s->stream));
+    if (!direct) QSV_HIP(s, hipMemcpyAsync(out, dout, ub, hipMemcpyDeviceToHost, s->stream));
     s->stats.kernels += 3;
     s->stats.alg_bytes += (double)s->dim() * s->elem();
-    return sync(s);
+    QSV_TRY(sync(s));
+    if (direct) std::memcpy(out, dout, ub);
+    return QSV_OK;
 }
 
 qsv_status qsv_get_state(qsv_sim *s, void *dst, int32_t dst_is_device) {
@@ -1426,7 +1421,7 @@ qsv_status qsv_set_state(qsv_sim *s, const void *src, int32_t src_is_device) {
     s->queue.clear();
     s->invalid = false;
     QSV_TRY(ensure_capacity(s, s->n));
-    QSV_TRY(ensure_small(s));
+    QSV_TRY(ensure_result(s));
     QSV_HIP(s, hipMemcpyAsync(s->d_state, src, s->dim() * s->elem(),
                               src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                               s->stream));
@@ -2054,7 +2049,7 @@ extern "C" qsv_status qsv_adjoint_gradient(qsv_sim *s, const qsv_circuit *circ,
     }
     const uint64_t dim = 1ull << n;
     QSV_TRY(ensure_vectors(s, dim));
-    QSV_TRY(ensure_small(s));
+    QSV_TRY(ensure_result(s));
     void *psi = s->d_vec[0], *phi = s->d_vec[1];
     // partial sums per rotation: nb per workgroup-wave of the tiled sweep
     // (mode TILED), else per workgroup of the per-gate reverse kernels
@@ -2120,7 +2115,7 @@ extern "C" qsv_status qsv_adjoint_gradient(qsv_sim *s, const qsv_circuit *circ,
                                    (const int32_t *)(w + off_ny), s->stream));
     double *partial = (double *)(w + off_pa);
     QSV_HIP(s, qsv::dev::dot_re(s->opt.dtype, psi, phi, dim, partial + (size_t)nb * nrot,
-                                s->d_small, s->stream));
+                                result(s), s->stream));
     // reverse sweep
     if (tiled)
         QSV_TRY(adjoint_reverse_tiled(s, gates, axis, circ->params, param, psi, phi, partial, grid,
@@ -2160,7 +2155,7 @@ extern "C" qsv_status qsv_adjoint_gradient(qsv_sim *s, const qsv_circuit *circ,
         QSV_HIP(s, hipMemcpyAsync(grad_out, dgrad, 8 * (size_t)circ->n_params,
                                   hipMemcpyDeviceToHost, s->stream));
     }
-    QSV_HIP(s, hipMemcpyAsync(value_out, s->d_small, sizeof(double), hipMemcpyDeviceToHost,
-                              s->stream));
-    return sync(s);
+    QSV_TRY(sync(s));
+    *value_out = *result(s);
+    return QSV_OK;
 }
