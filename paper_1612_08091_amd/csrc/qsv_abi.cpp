@@ -29,6 +29,7 @@
 #include "pauli.hpp"
 #include "qsv_internal.hpp"
 #include "tileprog.hpp"
+#include "trajectory.hpp"
 
 using qsv::cd;
 using qsv::Gate;
@@ -200,6 +201,7 @@ qsv_status invalid_state(qsv_sim *s) {
 // and indices there too, up to kDirectShots of them.
 constexpr size_t kDirectShots = 4096;
 constexpr size_t kResultBytes = 16 * kDirectShots;
+static_assert(kResultBytes >= sizeof(double) * qsv::dev::kGroupSums, "partial matrices");
 
 qsv_status ensure_result(qsv_sim *s) {
     if (!s->h_res) QSV_HIP(s, hipHostMalloc((void **)&s->h_res, kResultBytes, hipHostMallocDefault));
@@ -619,6 +621,60 @@ qsv_status do_flush(qsv_sim *s) {
     s->stats.amp_gate_updates += (double)s->queue.size() * (double)s->dim();
     s->queue.clear();
     return QSV_OK;
+}
+
+// The queued gates as one matrix over at most kGroupBits qubits, the group's
+// targets first; leaves the group without a matrix if they are on more.
+void group_queue(const qsv_sim *s, qsv::dev::GroupArgs &a) {
+    if (s->queue.empty()) return;
+    int bit[64];
+    std::fill(bit, bit + 64, -1);
+    for (int j = 0; j < a.kt; ++j) bit[a.pos[j]] = j;
+    int k = a.kt;
+    uint32_t pos[qsv::dev::kGroupBits] = {a.pos[0], a.pos[1], 0};
+    for (const Gate &g : s->queue) {
+        uint64_t all = g.ctrl;
+        for (int j = 0; j < g.k; ++j) all |= 1ull << g.t[j];
+        for (; all; all &= all - 1) {
+            const int p = __builtin_ctzll(all);
+            if (bit[p] >= 0) continue;
+            if (k == qsv::dev::kGroupBits) return;
+            pos[k] = (uint32_t)p;
+            bit[p] = k++;
+        }
+    }
+    const int D = 1 << k;
+    cd m[64] = {};
+    for (int r = 0; r < D; ++r) m[r * D + r] = 1.0;
+    for (const Gate &g : s->queue) {
+        const int d = 1 << g.k;
+        int off[8] = {0}, tm = 0, cm = 0;
+        for (int j = 0; j < g.k; ++j) {
+            tm |= 1 << bit[g.t[j]];
+            for (int r = 0; r < d; ++r)
+                if ((r >> j) & 1) off[r] |= 1 << bit[g.t[j]];
+        }
+        for (uint64_t c = g.ctrl; c; c &= c - 1) cm |= 1 << bit[__builtin_ctzll(c)];
+        for (int row = 0; row < D; ++row) {
+            if ((row & tm) || (row & cm) != cm) continue;
+            for (int c = 0; c < D; ++c) {
+                cd x[8], y;
+                for (int r = 0; r < d; ++r) x[r] = m[(row | off[r]) * D + c];
+                for (int r = 0; r < d; ++r) {
+                    y = 0.0;
+                    for (int e = 0; e < d; ++e) y += g.U[(size_t)r * d + e] * x[e];
+                    m[(row | off[r]) * D + c] = y;
+                }
+            }
+        }
+    }
+    a.apply = 1;
+    a.k = k;
+    for (int j = 0; j < k; ++j) a.pos[j] = pos[j];
+    for (int e = 0; e < D * D; ++e) {
+        a.ur[e] = m[e].real();
+        a.ui[e] = m[e].imag();
+    }
 }
 
 qsv_status sync(qsv_sim *s) {
@@ -1319,21 +1375,47 @@ qsv_status qsv_apply_kraus_sampled(qsv_sim *s, int32_t nk, const double *kraus, 
     const int D = 1 << k;
     for (int i = 0; i < nk * D * D * 2; ++i)
         if (!std::isfinite(kraus[i])) return fail(s, QSV_EINVAL, "non-finite Kraus entry");
-    QSV_TRY(do_flush(s));
+    // Reduced density matrix of the targets (bit j of its index = target j).  In
+    // mode TILED the waiting gates, where they and the targets are on at most
+    // three qubits, are applied in the same pass: a flush of its own would read
+    // and write the state once more.
+    qsv::dev::GroupArgs ga{};
+    ga.kt = k;
+    for (int j = 0; j < k; ++j) ga.pos[j] = (uint32_t)s->pos_of[targets[j]];
+    ga.k = k;
+    if (!s->invalid && s->opt.mode == QSV_MODE_TILED) group_queue(s, ga);
+    if (!ga.apply) QSV_TRY(do_flush(s));
     QSV_TRY(materialize(s));
-    // reduced density matrix of the targets (bit j of its index = target j)
-    int pos[2] = {s->pos_of[targets[0]], k > 1 ? s->pos_of[targets[1]] : 0};
-    QSV_TRY(ensure_ws(s, qsv::dev::reduced_dm_workspace_bytes()));
+    ga.nq = s->n;
+    if (ga.apply) QSV_TRY(launch_gate(s));
+    const double bytes = (ga.apply ? 2.0 : 1.0) * (double)s->dim() * s->elem();
+    int blocks = 0;
     const int tok = tbegin(s);
-    QSV_HIP(s, qsv::dev::reduced_dm(s->opt.dtype, s->d_state, s->n, k, pos, (double *)s->d_ws,
-                                    result(s), s->stream));
-    tend(s, tok, QSV_K_REDUCE, (double)s->dim() * s->elem());
-    s->stats.kernels += 2;
-    s->stats.alg_bytes += (double)s->dim() * s->elem();
+    QSV_HIP(s, qsv::dev::group_rdm(s->opt.dtype, s->d_state, ga, result(s), &blocks, s->stream));
+    tend(s, tok, ga.apply ? QSV_K_DENSE : QSV_K_REDUCE, bytes);
+    s->stats.kernels += 1;
+    s->stats.alg_bytes += bytes;
+    if (ga.apply) {
+        s->stats.passes += 1;
+        s->stats.fused_ops += 1;
+        s->stats.alg_flops += (8.0 * (1 << ga.k) - 2.0) * (double)s->dim();
+        s->stats.gates += s->queue.size();
+        s->stats.amp_gate_updates += (double)s->queue.size() * (double)s->dim();
+        s->queue.clear();
+    }
     QSV_TRY(sync(s));
-    const double *h = result(s);
+    const int width = qsv::dev::group_width(k);
+    double h[16] = {0.0};
+    for (int b = 0; b < blocks; ++b)
+        for (int e = 0; e < width; ++e) h[e] += result(s)[(size_t)b * width + e];
     std::vector<cd> rho((size_t)D * D);
-    for (int e = 0; e < D * D; ++e) rho[e] = cd(h[2 * e], h[2 * e + 1]);
+    for (int q = 0, w = D; q < D; ++q) {
+        rho[q * D + q] = h[q];
+        for (int p = 0; p < q; ++p, w += 2) {
+            rho[p * D + q] = cd(h[w], h[w + 1]);
+            rho[q * D + p] = cd(h[w], -h[w + 1]);
+        }
+    }
     // p_j = ||K_j psi||^2 = Tr(K_j rho K_j^dagger)
     std::vector<double> p(nk);
     double total = 0.0;
