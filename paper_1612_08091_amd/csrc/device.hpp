@@ -157,6 +157,8 @@ struct RegSeg {
     uint64_t state_off;
     int32_t ta;
     int32_t op_begin;
+    int32_t init;           // 1: the circuit's first pass (tiles start from |0...0>)
+    int32_t pad;
 };
 
 // ------------------------------------------------------------------ gates
@@ -297,16 +299,18 @@ struct BatchLaunch {
     const int32_t *seg_begin; // host, n_pass_launches + 2 entries
     const uint64_t *items;    // host, n_pass_launches + 1 entries
     void *states;
-    double *partial;          // one sum per Pauli work item
-    int32_t chunk_log;        // Pauli chunk: 2^chunk_log amplitudes (pairs for X strings)
+    double *partial;          // one sum per Pauli work item (chunks of 2^batch_chunk_log)
     unsigned int grid_big;
+    int32_t cus;
+    // beside pass-major launches: the stream of k_batch and its events
+    hipStream_t side;
+    hipEvent_t fork, join;
     // Pass-major circuits of at least 13 qubits run on the register-tile
     // kernel (12-bit tiles, the planning and lowering of the single-state
-    // path): their states (reg_amps amplitudes from amplitude reg_state_off
-    // of `states`, each starting at reg_starts[i]) are set to |0...0> first,
-    // then launch i < n_reg_launches runs segments [reg_seg_begin[i],
+    // path): launch i < n_reg_launches runs segments [reg_seg_begin[i],
     // reg_seg_begin[i + 1]) of reg_segs over reg_items[i] tiles, with the
-    // table-op instance where reg_dg[i].
+    // table-op instance where reg_dg[i]; a circuit's first pass starts from
+    // |0...0>.
     int32_t n_reg_launches;
     const RegSeg *reg_segs;
     const int32_t *reg_seg_begin; // host
@@ -316,10 +320,8 @@ struct BatchLaunch {
     const RegOp *rops;
     const void *reg_pool;         // LDS images
     uint32_t reg_img_max;
-    uint64_t reg_state_off, reg_amps;
-    const uint64_t *reg_starts;
-    int32_t n_reg_states;
 };
+inline int batch_chunk_log(int dtype) { return dtype == 0 ? 11 : 12; }
 hipError_t batch_launch(int dtype, const BatchLaunch &L, hipStream_t s);
 int batch_occupancy(int dtype, int mb, int mfma_k);   // resident workgroups per CU
 int batch_pass_occupancy(int dtype, int mb, int mfma_k);

@@ -76,6 +76,9 @@ struct qsv_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
+    // the stream of the circuits in LDS beside pass-major launches
+    hipStream_t side = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
     double last_ms = 0.0;
 };
 
@@ -178,7 +181,7 @@ const qsv_batch::RegPlan &reg_plan(qsv_batch *b, int i) {
         if (pg.rops.empty() && !pg.permutes) continue;
         rp.progs.push_back(std::move(pg));
     }
-    rp.ok = true;
+    rp.ok = !rp.progs.empty();      // the first pass writes the state
     return rp;
 }
 
@@ -297,18 +300,15 @@ qsv_status build_plan(qsv_batch *b, int mb, int kf) {
     b->h_items.clear();
     int n_pass_launches = 0;
     // Pauli chunk per work item, held in LDS: 32 KiB
-    const int kChunkLog = b->dtype == QSV_C128 ? 11 : 12;
+    const int kChunkLog = qsv::dev::batch_chunk_log(b->dtype);
     // register-path circuits (at least 13 qubits, every pass lowered to the
-    // register kernel) and LDS-path ones; states: LDS-path first, then the
-    // register-path ones in one range (set to |0...0> by one fill)
+    // register kernel) and LDS-path ones
     std::vector<int> big_lds, big_reg;
     std::vector<qsv::dev::TileArgs> tas;
     std::vector<qsv::dev::RegOp> rops;
     std::vector<unsigned char> imgs;
     std::vector<qsv::dev::RegSeg> rsegs;
-    std::vector<uint64_t> reg_starts;
     uint32_t img_max = 0;
-    uint64_t reg_state_off = 0, reg_amps = 0;
     b->h_reg_seg_begin.clear();
     b->h_reg_items.clear();
     b->h_reg_dg.clear();
@@ -323,13 +323,10 @@ qsv_status build_plan(qsv_batch *b, int mb, int kf) {
             state_off[i] = off;
             off += 1ull << b->nq[i];
         }
-        reg_state_off = off;
         for (int i : big_reg) {
             state_off[i] = off;
-            reg_starts.push_back(off);
             off += 1ull << b->nq[i];
         }
-        reg_amps = off - reg_state_off;
         // register launches: pass p of every register-path circuit that has one
         std::vector<std::vector<int>> ta_of(b->count), op_of(b->count);
         for (int i : big_reg) {
@@ -357,6 +354,7 @@ qsv_status build_plan(qsv_batch *b, int mb, int kf) {
                 sg.state_off = state_off[i];
                 sg.ta = ta_of[i][p];
                 sg.op_begin = op_of[i][p];
+                sg.init = p == 0 ? 1 : 0;
                 rsegs.push_back(sg);
                 it += tas[sg.ta].n_tiles;
                 if (!tas[sg.ta].no_diag) dg = 1;
@@ -422,7 +420,6 @@ qsv_status build_plan(qsv_batch *b, int mb, int kf) {
     const size_t o_rops = put(host, rops);
     const size_t o_imgs = put(host, imgs);
     const size_t o_rsegs = put(host, rsegs);
-    const size_t o_rstarts = put(host, reg_starts);
     const size_t o_part = put(host, std::vector<double>(pm ? b->h_items.back() : 1, 0.0));
     hipError_t e = hipMalloc(&b->d_buf, host.size());
     if (e != hipSuccess) return berr(QSV_ENOMEM, "hipMalloc of the batch plan failed");
@@ -478,16 +475,21 @@ qsv_status build_plan(qsv_batch *b, int mb, int kf) {
     L.rops = (const qsv::dev::RegOp *)(d + o_rops);
     L.reg_pool = d + o_imgs;
     L.reg_img_max = img_max;
-    L.reg_state_off = reg_state_off;
-    L.reg_amps = reg_amps;
-    L.reg_starts = (const uint64_t *)(d + o_rstarts);
-    L.n_reg_states = (int32_t)reg_starts.size();
     L.segs = (const qsv::dev::BatchSeg *)(d + o_segs);
     L.seg_begin = b->h_seg_begin.data();
     L.items = b->h_items.data();
     L.states = b->d_states;
     L.partial = (double *)(d + o_part);
-    L.chunk_log = kChunkLog;
+    L.cus = std::max(1, cus);
+    if (pm && !b->side) {
+        e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
+        if (e != hipSuccess) return berr(QSV_EDEVICE, std::string("stream/event: ") + hipGetErrorString(e));
+    }
+    L.side = b->side;
+    L.fork = b->fork;
+    L.join = b->join;
     L.grid_big = (unsigned)(cus * std::max(1, qsv::dev::batch_pass_occupancy(b->dtype, mb, mfma_k)));
     b->mb = mb;
     b->kfuse = kf;
@@ -680,6 +682,9 @@ qsv_status qsv_batch_destroy(qsv_batch *b) {
     if (b->d_states) (void)hipFree(b->d_states);
     if (b->e0) (void)hipEventDestroy(b->e0);
     if (b->e1) (void)hipEventDestroy(b->e1);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    if (b->join) (void)hipEventDestroy(b->join);
+    if (b->side) (void)hipStreamDestroy(b->side);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return QSV_OK;

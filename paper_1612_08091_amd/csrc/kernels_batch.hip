@@ -22,6 +22,14 @@ __constant__ uint32_t kIdentityPos[40] = {0,  1,  2,  3,  4,  5,  6,  7,  8,  9,
                                           14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27,
                                           28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39};
 
+// The chip's XCDs; workgroup w runs on XCD w mod 8.
+constexpr unsigned kXcds = 8;
+
+// +1 or -1 by bit 0 of s
+__device__ __forceinline__ double sign_of(uint32_t s) {
+    return __hiloint2double((int)(0x3ff00000u | (s << 31)), 0);
+}
+
 template <typename R>
 __device__ __forceinline__ double block_sum_b(double v, double *sh) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
@@ -260,30 +268,6 @@ __global__ __launch_bounds__(kNT) void k_batch(const BatchCircuit *__restrict__ 
 __global__ void k_reset_counter(unsigned int *counter) { *counter = 0u; }
 
 // ------------------------------------------------------ pass-major circuits
-// |0...0> in the states of the register-path circuits: the region zeroed,
-// then amplitude 0 of each state set to 1.
-template <typename R>
-__global__ void k_batch_zero(typename VT<R>::T *p, uint64_t n) {
-    using T = typename VT<R>::T;
-    T z;
-    z.x = R(0);
-    z.y = R(0);
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = z;
-}
-template <typename R>
-__global__ void k_batch_one(typename VT<R>::T *states, const uint64_t *__restrict__ starts,
-                            int count) {
-    using T = typename VT<R>::T;
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= count) return;
-    T o;
-    o.x = R(1);
-    o.y = R(0);
-    states[starts[i]] = o;
-}
-
 // Segment of work item `it`: the last segment whose first item is <= it (the
 // host orders a launch's segments by first item, the first one at 0).
 __device__ __forceinline__ int find_seg(const BatchSeg *__restrict__ segs, int nseg,
@@ -319,100 +303,109 @@ __global__ __launch_bounds__(kNT) void k_batch_pass(const BatchSeg *__restrict__
 
 // The Pauli sums of the pass-major circuits: work item = (circuit, chunk k of
 // C = 2^cl indices, cl = min(chunk_log, n)); partial[item] = the chunk's
-// share of sum_t c_t <P_t>.  The chunk is read into LDS once and serves
-// every term.  A term with X letters pairs j with j ^ x; the pair is taken
-// by the chunk of its member with bit h = 0 (h: the highest X bit): within
-// the chunk when h < cl, else by the chunks whose index has bit h - cl clear,
-// which read the partner chunk k ^ (x >> cl) from global memory.  So a term
-// reads half a state from global memory instead of a whole one, and a
-// string of Z letters none.
+// share of sum_t c_t <P_t>.  The chunk is read once, into registers (NR
+// amplitudes per thread) and into LDS, and serves every term.  A term with X
+// letters pairs j with j ^ x; the pair is taken by the chunk of its member with
+// bit h = 0 (h: the highest X bit): within the chunk when h < cl, else by the
+// chunks whose index has bit h - cl clear, which read the partner chunk
+// k ^ (x >> cl) from memory.  So a term reads half a state from memory instead
+// of a whole one, and a string of Z letters none.
+// A pair costs one product (Re or Im of conj(b) a, by the parity of n_Y) and a
+// signed add: the sign splits into the chunk's and thread's, which go in with
+// the coefficient, and the register's, uniform.  Workgroups of one XCD take a
+// contiguous range of the items, so that a circuit's chunks are read again from
+// that XCD's L2.  Bound by those reads and the products together: 192 circuits
+// of 8 to 20 qubits with 64 strings each (complex64) 0.57 ms, 14 TB/s of partner
+// reads; 1.20 with four sign tests and both products per pair and chunks dealt
+// out over all XCDs.
 template <typename R>
 __global__ __launch_bounds__(kNT) void k_batch_pauli(const BatchSeg *__restrict__ segs, int nseg,
                                                      uint64_t items,
                                                      const BatchCircuit *__restrict__ circuits,
                                                      const BatchTerm *__restrict__ terms,
                                                      const typename VT<R>::T *__restrict__ states,
-                                                     int chunk_log, double *__restrict__ partial) {
+                                                     double *__restrict__ partial) {
     using T = typename VT<R>::T;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T *ch = reinterpret_cast<T *>(smem_raw);
+    constexpr int RBITS = sizeof(R) == 4 ? 4 : 3, NR = 1 << RBITS;
+    constexpr int LOG = 8 + RBITS;
+    static_assert(kNT == 256, "thread bits");
+    __shared__ __align__(16) T ch[1 << LOG];
     __shared__ double sh[16];
-    constexpr int U = sizeof(R) == 4 ? 8 : 4;   // global reads in flight per thread
     const uint32_t tid = threadIdx.x;
-    for (uint64_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const uint64_t xcd = blockIdx.x & (kXcds - 1), per = gridDim.x / kXcds;
+    const uint64_t it1 = items * (xcd + 1) / kXcds;
+    for (uint64_t it = items * xcd / kXcds + blockIdx.x / kXcds; it < it1; it += per) {
         const BatchSeg sg = segs[find_seg(segs, nseg, it)];
         const BatchCircuit bc = circuits[sg.circuit];
-        const int cl = chunk_log < bc.n ? chunk_log : bc.n;
+        const int cl = LOG < bc.n ? LOG : bc.n;
         const uint32_t C = 1u << cl;
-        const uint64_t k = it - sg.first;
-        const uint64_t j0 = k << cl;
+        const uint64_t j0 = (it - sg.first) << cl;
         const T *st = states + sg.state_off;
-        {
-            // U loads of a thread out together before their LDS writes
-            uint32_t l = tid;
-            for (; l + (U - 1) * kNT < C; l += U * kNT) {
-                T v[U];
+        T a[NR];
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = st[j0 + l + u * kNT];
-#pragma unroll
-                for (int u = 0; u < U; ++u) ch[l + u * kNT] = v[u];
-            }
-            for (; l < C; l += kNT) ch[l] = st[j0 + l];
+        for (int u = 0; u < NR; ++u) {
+            a[u].x = a[u].y = R(0);
+            if ((uint32_t)u * kNT + tid < C) a[u] = st[j0 + (uint32_t)u * kNT + tid];
         }
+#pragma unroll
+        for (int u = 0; u < NR; ++u) ch[(uint32_t)u * kNT + tid] = a[u];
         __syncthreads();
         double acc = 0.0;
         for (int t = 0; t < bc.term_count; ++t) {
-            const BatchTerm tm = terms[bc.term_begin + t];
-            double sr = 0.0, si = 0.0;
-            if (tm.x == 0) {
-                for (uint32_t l = tid; l < C; l += kNT) {
-                    const T a = ch[l];
-                    const double p = (double)a.x * a.x + (double)a.y * a.y;
-                    sr += (__popcll((j0 + l) & tm.z) & 1) ? -p : p;
+            const BatchTerm &tm = terms[bc.term_begin + t];
+            const uint64_t x = tm.x, z = tm.z;
+            const int h = x ? 63 - __builtin_clzll(x) : -1;
+            const bool far = h >= cl;
+            if (far && ((j0 >> h) & 1)) continue;
+            const uint32_t xthr = (uint32_t)x & (kNT - 1), xr = ((uint32_t)x & (C - 1)) >> 8;
+            // registers that stand for pairs: all, or those with the highest X
+            // bit clear where it is a register bit
+            uint32_t take = (1u << NR) - 1;
+            if (!far && xr) {
+                const int hb = 31 - __builtin_clz(xr);
+                take &= hb == 0 ? 0x5555u : hb == 1 ? 0x3333u : hb == 2 ? 0x0f0fu : 0x00ffu;
+            }
+            T b[NR];
+            if (far) {
+                const T *pp = st + ((j0 ^ x) & ~(uint64_t)(C - 1));
+#pragma unroll
+                for (int u = 0; u < NR; ++u) b[u] = pp[(((uint32_t)u ^ xr) << 8) + (tid ^ xthr)];
+            } else {
+#pragma unroll
+                for (int u = 0; u < NR; ++u) b[u] = ch[(((uint32_t)u ^ xr) << 8) + (tid ^ xthr)];
+            }
+            // sign of register u: parity of u and the Z mask's register bits
+            const uint32_t zr = (uint32_t)(z >> 8);
+            uint32_t sreg = 0;
+            if (zr & 1) sreg ^= 0xaaaau;
+            if (zr & 2) sreg ^= 0xccccu;
+            if (zr & 4) sreg ^= 0xf0f0u;
+            if (NR > 8 && (zr & 8)) sreg ^= 0xff00u;
+            double local = 0.0;
+            if (tm.ny & 1) {
+#pragma unroll
+                for (int u = 0; u < NR; ++u) {
+                    if (!((take >> u) & 1)) continue;
+                    const double q = __builtin_fma((double)b[u].x, (double)a[u].y,
+                                                   -((double)b[u].y * (double)a[u].x));
+                    local = __builtin_fma(q, sign_of(sreg >> u), local);
                 }
             } else {
-                const int h = 63 - __builtin_clzll(tm.x);
-                auto add = [&](uint64_t j, const T &a, const T &b) {
-                    const uint64_t j2 = j ^ tm.x;
-                    const double u = (double)b.x * a.x + (double)b.y * a.y;
-                    const double v = (double)b.x * a.y - (double)b.y * a.x;
-                    const double s1 = (__popcll(j & tm.z) & 1) ? -1.0 : 1.0;
-                    const double s2 = (__popcll(j2 & tm.z) & 1) ? -1.0 : 1.0;
-                    sr += (s1 + s2) * u;
-                    si += (s1 - s2) * v;
-                };
-                if (h < cl) {
-                    // both members in the chunk: pair g has local index g
-                    // with a 0 inserted at bit h
-                    const uint32_t lowm = (1u << h) - 1;
-                    const uint32_t xl = (uint32_t)tm.x;
-                    for (uint32_t g = tid; g < (C >> 1); g += kNT) {
-                        const uint32_t l = ((g & ~lowm) << 1) | (g & lowm);
-                        add(j0 + l, ch[l], ch[l ^ xl]);
-                    }
-                } else if (((j0 >> h) & 1) == 0) {
-                    const T *pp = st + ((j0 ^ tm.x) & ~(uint64_t)(C - 1));
-                    const uint32_t xl = (uint32_t)(tm.x & (C - 1));
-                    uint32_t l = tid;
-                    for (; l + (U - 1) * kNT < C; l += U * kNT) {
-                        T b[U];
 #pragma unroll
-                        for (int u = 0; u < U; ++u) b[u] = pp[(l + u * kNT) ^ xl];
-#pragma unroll
-                        for (int u = 0; u < U; ++u) add(j0 + l + u * kNT, ch[l + u * kNT], b[u]);
-                    }
-                    for (; l < C; l += kNT) add(j0 + l, ch[l], pp[l ^ xl]);
+                for (int u = 0; u < NR; ++u) {
+                    if (!((take >> u) & 1)) continue;
+                    const double q = __builtin_fma((double)b[u].x, (double)a[u].x,
+                                                   (double)b[u].y * (double)a[u].y);
+                    local = __builtin_fma(q, sign_of(sreg >> u), local);
                 }
             }
-            // Re(i^{ny} (sr + i si))
-            double re;
-            switch (tm.ny & 3) {
-            case 0: re = sr; break;
-            case 1: re = -si; break;
-            case 2: re = -sr; break;
-            default: re = si; break;
-            }
-            acc += tm.c * re;
+            // i^{ny} times the pair's 2 Re (ny even) or 2 i Im (odd); without X
+            // letters, or where both members of every pair are summed, 1
+            const int ny = tm.ny & 3;
+            double c = ny == 0 || ny == 3 ? tm.c : -tm.c;
+            if (far || xr) c *= 2.0;
+            const uint32_t s = (uint32_t)(__popcll(j0 & z) + __popc(tid & (uint32_t)z)) & 1u;
+            acc = __builtin_fma(local, s ? -c : c, acc);
         }
         const double tot = block_sum_b<R>(acc, sh);
         if (tid == 0) partial[it] = tot;
@@ -420,17 +413,20 @@ __global__ __launch_bounds__(kNT) void k_batch_pauli(const BatchSeg *__restrict_
     }
 }
 
-// <H> of each pass-major circuit: its chunk sums added in chunk order (the
-// same order on every run).
-__global__ void k_batch_finish(const BatchSeg *__restrict__ segs, int nseg, uint64_t items,
-                               const BatchCircuit *__restrict__ circuits,
-                               const double *__restrict__ partial, double *__restrict__ out) {
-    const int s = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+// <H> of each pass-major circuit: its chunk sums added by one wave in a fixed
+// order (the same on every run).
+__global__ __launch_bounds__(256) void k_batch_finish(const BatchSeg *__restrict__ segs, int nseg,
+                                                      uint64_t items,
+                                                      const BatchCircuit *__restrict__ circuits,
+                                                      const double *__restrict__ partial,
+                                                      double *__restrict__ out) {
+    const int s = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
     if (s >= nseg) return;
     const uint64_t b = segs[s].first, e = s + 1 < nseg ? segs[s + 1].first : items;
     double acc = 0.0;
-    for (uint64_t i = b; i < e; ++i) acc += partial[i];
-    out[circuits[segs[s].circuit].out_index] = acc;
+    for (uint64_t i = b + lane; i < e; i += 64) acc += partial[i];
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+    if (lane == 0) out[circuits[segs[s].circuit].out_index] = acc;
 }
 
 template <typename R, int KM>
@@ -445,29 +441,31 @@ static hipError_t batch_t(const BatchLaunch &L, hipStream_t s) {
         attr = lds;
     }
     if (L.count > 0) {
-        hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, s, L.counter);
-        hipLaunchKernelGGL((k_batch<R, KM>), dim3(L.grid), dim3(kNT), lds, s, L.circuits,
+        // Beside pass-major launches the circuits in LDS run on a stream of
+        // their own: they share nothing but the plan, and alone they leave most
+        // of the chip idle.
+        hipStream_t w = s;
+        if (L.pass_major) {
+            w = L.side;
+            hipError_t e = hipEventRecord(L.fork, s);
+            if (e == hipSuccess) e = hipStreamWaitEvent(w, L.fork, 0);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, w, L.counter);
+        hipLaunchKernelGGL((k_batch<R, KM>), dim3(L.grid), dim3(kNT), lds, w, L.circuits,
                            L.order, L.count, L.passes, L.ops, (const T *)L.pool, L.terms,
                            (T *)L.scratch, L.slot_amps, L.mb, L.counter, L.out);
         hipError_t e = hipGetLastError();
+        if (e == hipSuccess && L.pass_major) e = hipEventRecord(L.join, w);
         if (e != hipSuccess) return e;
     }
     if (!L.pass_major) return hipSuccess;
-    if (L.n_reg_launches > 0) {
-        T *rs = (T *)L.states + L.reg_state_off;
-        const unsigned zg = (unsigned)std::min<uint64_t>((L.reg_amps + 255) / 256, 65536);
-        hipLaunchKernelGGL((k_batch_zero<R>), dim3(zg), dim3(256), 0, s, rs, L.reg_amps);
-        hipLaunchKernelGGL((k_batch_one<R>), dim3((L.n_reg_states + 255) / 256), dim3(256), 0, s,
-                           (T *)L.states, L.reg_starts, L.n_reg_states);
-        hipError_t e = hipGetLastError();
+    for (int i = 0; i < L.n_reg_launches; ++i) {
+        const int sb = L.reg_seg_begin[i], ns = L.reg_seg_begin[i + 1] - sb;
+        hipError_t e = launch_tile_reg_batch(sizeof(R) == 8 ? 0 : 1, L.reg_dg[i] != 0, L.states,
+                                             L.reg_segs + sb, ns, L.reg_items[i], L.tas, L.rops,
+                                             L.reg_pool, L.reg_img_max, s);
         if (e != hipSuccess) return e;
-        for (int i = 0; i < L.n_reg_launches; ++i) {
-            const int sb = L.reg_seg_begin[i], ns = L.reg_seg_begin[i + 1] - sb;
-            e = launch_tile_reg_batch(sizeof(R) == 8 ? 0 : 1, L.reg_dg[i] != 0, L.states,
-                                      L.reg_segs + sb, ns, L.reg_items[i], L.tas, L.rops,
-                                      L.reg_pool, L.reg_img_max, s);
-            if (e != hipSuccess) return e;
-        }
     }
     static size_t attr_p = 0;
     if (attr_p < lds) {
@@ -485,26 +483,22 @@ static hipError_t batch_t(const BatchLaunch &L, hipStream_t s) {
             hipLaunchKernelGGL((k_batch_pass<R, KM>), dim3(grid), dim3(kNT), lds, s, L.segs + sb,
                                ns, items, L.passes, L.ops, (const T *)L.pool, (T *)L.states);
         } else {
-            const size_t chb = sizeof(T) << L.chunk_log;
-            static size_t attr_c = 0;
-            if (attr_c < chb) {
-                hipError_t e = hipFuncSetAttribute((const void *)k_batch_pauli<R>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   (int)chb);
-                if (e != hipSuccess) return e;
-                attr_c = chb;
-            }
-            hipLaunchKernelGGL((k_batch_pauli<R>), dim3(grid), dim3(kNT), chb, s, L.segs + sb, ns,
-                               items, L.circuits, L.terms, (const T *)L.states, L.chunk_log,
-                               L.partial);
-            hipLaunchKernelGGL(k_batch_finish, dim3((ns + 255) / 256), dim3(256), 0, s,
-                               L.segs + sb, ns, items, L.circuits, (const double *)L.partial,
-                               L.out);
+            int occ = 0;
+            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &occ, reinterpret_cast<const void *>(k_batch_pauli<R>), kNT, 0);
+            if (e != hipSuccess) return e;
+            // whole rounds of the XCDs
+            const uint64_t most = (uint64_t)L.cus * std::max(1, occ);
+            const unsigned pg = (unsigned)(std::max<uint64_t>(1, std::min(items, most) / kXcds) * kXcds);
+            hipLaunchKernelGGL((k_batch_pauli<R>), dim3(pg), dim3(kNT), 0, s, L.segs + sb, ns, items,
+                               L.circuits, L.terms, (const T *)L.states, L.partial);
+            hipLaunchKernelGGL(k_batch_finish, dim3((ns + 3) / 4), dim3(256), 0, s, L.segs + sb, ns,
+                               items, L.circuits, (const double *)L.partial, L.out);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    return L.count > 0 ? hipStreamWaitEvent(s, L.join, 0) : hipSuccess;
 }
 
 // Kernel variant for the widest matrix-core op of the batch: up to 3 qubits

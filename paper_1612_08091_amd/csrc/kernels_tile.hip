@@ -651,7 +651,14 @@ __global__ __launch_bounds__(1 << TB) void k_tile_reg_batch(typename VT<R>::T *_
         const RegOp *prog = ops + sg.op_begin;
         const int n_ops = ta.n_ops;
         T amp[NR];
-        load_tile<T, RB, m>(amp, psi, gl, tile, ta);
+        if (sg.init) {
+            // |0...0>: not read, and never written before
+#pragma unroll
+            for (int i = 0; i < NR; ++i) amp[i].x = amp[i].y = R(0);
+            if (tile == 0 && tid == 0) amp[0].x = R(1);
+        } else {
+            load_tile<T, RB, m>(amp, psi, gl, tile, ta);
+        }
         const uint64_t base = tile_base<m>(tile, ta);
         for (int oi = 0; oi < n_ops; oi += 2) {
             reg_op<T, R, NR, RB, DG>(amp, prog[oi], lds_a, limg_a, base, lane, wave);
