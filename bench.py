@@ -45,6 +45,8 @@ FP64_PEAK = 78.6e12        # MI355X FP64 (vector and matrix), flop/s
 TRAFFIC = {"kernel": "k_tile_reg<double,4,8,*>", "fetch_kib": 8394362.6, "write_kib": 16785437.0,
            "fetch_scale": 2.0, "write_scale": 1.0, "digest": "8a514cddf6243155"}
 TRAFFIC_SOURCES = ("paper_1612_08091_amd/csrc/kernels_tile.hip",
+                   "paper_1612_08091_amd/csrc/kernels_tile_reg_f64.hip",
+                   "paper_1612_08091_amd/csrc/tile_reg.hpp",
                    "paper_1612_08091_amd/csrc/lds_ops.hpp",
                    "paper_1612_08091_amd/csrc/device.hpp",
                    "paper_1612_08091_amd/csrc/tileprog.cpp",

@@ -64,8 +64,8 @@ struct TileArgs {
     uint64_t n_tiles;
     int32_t rb;           // register bits per thread (threads = 2^(m - rb))
     int32_t mfma_k;       // LDS kernel: widest matrix-core op of the pass (0 = none)
-    int32_t no_diag;      // register kernel: 1 if the program has no ROP_DIAG op (a
-                          // leaner kernel instance without that case runs it)
+    int32_t tables;       // register kernel: 0 without table ops, 1 with DIAG, 2 with DGRP too
+                          // (the leanest instance of the kernel runs it)
     uint32_t img_bytes;   // register kernel: bytes of the pass's LDS image (multiple of 16)
     int32_t store_sync;   // register kernel: 1 = workgroup barrier between the ops and the
                           // stores (the stores go where other threads loaded)
@@ -87,8 +87,25 @@ struct TileArgs {
 //          is real up to diagonal phases on either side; the phases become
 //          DIAG ops), half the arithmetic of G1/G2 per amplitude.
 //   DIAG:  per-amplitude factor from a table in the pass's LDS image.
+//   DGRP:  several tables whose register bits are at most two in all: their
+//          factors for the at most four values of those bits are multiplied
+//          first, then applied to the amplitudes once.
 //   REMAP: layout change through the LDS half-tile buffer.
-enum RegOpKind : int32_t { ROP_G1 = 0, ROP_G2 = 1, ROP_DIAG = 2, ROP_REMAP = 3, ROP_R1 = 5, ROP_R2 = 6 };
+enum RegOpKind : int32_t { ROP_G1 = 0, ROP_G2 = 1, ROP_DIAG = 2, ROP_REMAP = 3, ROP_DGRP = 4,
+                           ROP_R1 = 5, ROP_R2 = 6,
+                           ROP_CTRL = 16 };   // added to G/R kinds under controls
+// One table of a DGRP op.  A place is the number of a table bit (byte weight =
+// element size << place), four bits each, 15 for none.
+struct DiagTab {
+    uint32_t off, ones;   // byte offsets in the image, as DIAG's mat and b
+    uint64_t octrl;
+    uint64_t gpos;        // positions of the table bits outside the tile, a byte each
+    uint32_t gplace;      // their places
+    uint32_t lane;        // places of lane bits 0..5, then the count of outside bits
+    uint32_t wave;        // places of wave bits 0..2, then of the op's register bits
+    uint32_t pad;
+};
+constexpr int kDiagGroup = 9;   // tables of a DGRP op, at most
 // Widest diagonal op of the register kernel (table bits; its table of 2^k
 // factors lives in the pass's LDS image).
 constexpr int kRegDiagMax = 8;
@@ -144,6 +161,7 @@ struct RegOp {
             uint32_t rd[32];      // REMAP: buffer byte offset of register i in the new layout;
                                   // DIAG: see lane_ok
         };
+        DiagTab dt[kDiagGroup];   // DGRP: a tables, creg the mask of register bits
     };
     uint32_t pad_[4];
 };
@@ -175,7 +193,7 @@ hipError_t launch_tile_pass(int dtype, void *psi, const TileArgs &ta, const Tile
 // Batched register-tile launch (12-bit tiles, 16 amplitudes per thread):
 // items work items over the segments, a fixed stride per workgroup; img_max:
 // the largest image of the segments' passes.
-hipError_t launch_tile_reg_batch(int dtype, bool dg, void *states, const RegSeg *segs, int nseg,
+hipError_t launch_tile_reg_batch(int dtype, int dg, void *states, const RegSeg *segs, int nseg,
                                  uint64_t items, const TileArgs *tas, const RegOp *rops,
                                  const void *pool, uint32_t img_max, hipStream_t s);
 hipError_t launch_tile_reg(int dtype, void *psi, const TileArgs &ta, const RegOp *rops,

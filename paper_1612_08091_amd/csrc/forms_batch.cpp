@@ -203,9 +203,7 @@ qsv::dev::TileArgs reg_args(const qsv::TileProgram &pg, int n, int64_t img_off) 
     ta.img_off = img_off;
     ta.rb = 4;
     ta.n_ops = (int32_t)pg.rops.size();
-    ta.no_diag = 1;
-    for (const qsv::dev::RegOp &r : pg.rops)
-        if (r.kind == qsv::dev::ROP_DIAG) ta.no_diag = 0;
+    ta.tables = pg.tables();
     for (int b2 = 0; b2 < pg.m; ++b2) ta.spos[b2] = pg.spos[b2];
     return ta;
 }
@@ -357,7 +355,7 @@ qsv_status build_plan(qsv_batch *b, int mb, int kf) {
                 sg.init = p == 0 ? 1 : 0;
                 rsegs.push_back(sg);
                 it += tas[sg.ta].n_tiles;
-                if (!tas[sg.ta].no_diag) dg = 1;
+                dg = std::max(dg, (int)tas[sg.ta].tables);
             }
             b->h_reg_items.push_back(it);
             b->h_reg_dg.push_back(dg);

@@ -462,7 +462,7 @@ static hipError_t batch_t(const BatchLaunch &L, hipStream_t s) {
     if (!L.pass_major) return hipSuccess;
     for (int i = 0; i < L.n_reg_launches; ++i) {
         const int sb = L.reg_seg_begin[i], ns = L.reg_seg_begin[i + 1] - sb;
-        hipError_t e = launch_tile_reg_batch(sizeof(R) == 8 ? 0 : 1, L.reg_dg[i] != 0, L.states,
+        hipError_t e = launch_tile_reg_batch(sizeof(R) == 8 ? 0 : 1, L.reg_dg[i], L.states,
                                              L.reg_segs + sb, ns, L.reg_items[i], L.tas, L.rops,
                                              L.reg_pool, L.reg_img_max, s);
         if (e != hipSuccess) return e;

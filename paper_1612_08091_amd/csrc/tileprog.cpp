@@ -269,6 +269,7 @@ struct ImgBlock {
     int op = -1;          // index into rops
     bool table = false;   // patches rops[op].mat (else lane_off)
     bool ones = false;    // a table of ones: patches rops[op].b instead
+    int sub = -1;         // a table of a DGRP op: its place in dt
     uint32_t off = 0;
 };
 
@@ -482,7 +483,9 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
     // Steps 3b-4 build the program with tables of at most `cap` qubits and
     // return the size of its LDS image.
     const int real_ops = prog.real_ops;
-    auto lower = [&](int cap) -> uint32_t {
+    int saved = 0;   // ops that groups of tables take out (or would)
+    auto lower = [&](int cap, bool group) -> uint32_t {
+    saved = 0;
     mats.resize(mats_mark);
     prog.rops.clear();
     prog.img.clear();
@@ -704,6 +707,183 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
         return -1;
     };
 
+    // A diagonal item as a table op in the current layout.
+    struct Table {
+        dev::RegOp r{};
+        uint32_t regs = 0;              // register bits that are table bits
+        int place[5] = {};              // their table bits
+        std::vector<ImgBlock> blocks;
+    };
+    auto make_table = [&](const Item &it) {
+        Table out;
+        dev::RegOp &r = out.r;
+        r.kind = dev::ROP_DIAG;
+        // table bits: every qubit of the members except the controls that
+        // all of them share and that lie outside the tile
+        uint64_t common = ~0ull;
+        for (const Op &o : it.members) common &= o.ctrl;
+        const uint64_t octrl = common & ~tile_mask;
+        const uint64_t tq_mask = it.all & ~octrl;
+        // table bit order: the qubits on lane bits first, by lane bit, so
+        // that the 16 lanes a ds_read_b128 serves together (lane bits 0-3)
+        // read distinct 16-byte slots of one 256-byte bank row, or the
+        // same slot (a broadcast): no bank conflicts
+        int tq[dev::kRegDiagMax], kt = 0;
+        for (int t = 0; t < lane_bits; ++t)
+            for (int p = 0; p < 64; ++p)
+                if (((tq_mask >> p) & 1) && li[p] >= 0 && slot_of(p) < 0 && thr_of(p) == t)
+                    tq[kt++] = p;
+        for (int p = 0; p < 64; ++p) {
+            if (!((tq_mask >> p) & 1)) continue;
+            const int t = li[p] >= 0 && slot_of(p) < 0 ? thr_of(p) : -1;
+            if (t < 0 || t >= lane_bits) tq[kt++] = p;
+        }
+        r.octrl = octrl;
+        const uint32_t eb = (uint32_t)elem_bytes;
+        for (int j = 0; j < kt; ++j) {
+            const uint32_t wgt = eb << j;
+            if (li[tq[j]] < 0) {
+                r.gt[r.a] = (uint32_t)tq[j];
+                r.gtb[r.a] = wgt;
+                r.a += 1;
+                continue;
+            }
+            const int sj = slot_of(tq[j]);
+            if (sj >= 0) {
+                out.regs |= 1u << sj;
+                out.place[sj] = j;
+                for (int x = 0; x < nr; ++x)
+                    if ((x >> sj) & 1) r.wr[x] |= wgt;
+            } else {
+                const int t = thr_of(tq[j]);
+                if (t >= lane_bits)
+                    for (int w = 0; w < nwaves; ++w)
+                        if ((w >> (t - lane_bits)) & 1) r.wwave[w] |= wgt;
+            }
+        }
+        // lane thread-id bit t that is table bit j: bit t of lane_ok set,
+        // rd[t] = the bit's place in the byte offset (j + log2 eb)
+        r.lane_ok = 0;
+        for (int j = 0; j < kt; ++j) {
+            const int t = li[tq[j]] >= 0 && slot_of(tq[j]) < 0 ? thr_of(tq[j]) : -1;
+            if (t >= 0 && t < lane_bits) {
+                r.lane_ok |= 1ull << t;
+                r.rd[t] = (uint32_t)(j + __builtin_ctz(eb));
+            }
+        }
+        ImgBlock tab;
+        int changed = 0;
+        for (uint32_t row = 0; row < (1u << kt); ++row) {
+            uint64_t bits = octrl;
+            for (int j = 0; j < kt; ++j)
+                if ((row >> j) & 1) bits |= 1ull << tq[j];
+            cd v(1, 0);
+            for (const Op &o : it.members) {
+                if ((bits & o.ctrl) != o.ctrl) continue;
+                uint32_t rix = 0;
+                for (int j = 0; j < o.k; ++j)
+                    if ((bits >> o.t[j]) & 1) rix |= 1u << j;
+                v *= o.U[rix];
+            }
+            if (v != cd(1, 0)) ++changed;
+            put_complex(tab.bytes, v, elem_bytes);
+        }
+        tab.align = std::max<uint32_t>(16u, eb << kt);
+        tab.table = true;
+        if (octrl) {
+            // tiles that fail the controls outside the tile read ones
+            ImgBlock ones;
+            for (uint32_t row = 0; row < (1u << kt); ++row) put_complex(ones.bytes, cd(1, 0), elem_bytes);
+            ones.align = tab.align;
+            ones.table = true;
+            ones.ones = true;
+            out.blocks.push_back(std::move(ones));
+        }
+        out.blocks.push_back(std::move(tab));
+        prog.diag_ops += 1;
+        (void)changed;
+        return out;
+    };
+    // Puts a table at place `sub` of op `op` (a DGRP), or as an op of its own.
+    auto put_blocks = [&](Table &tb, int sub) {
+        for (ImgBlock &blk : tb.blocks) {
+            blk.op = (int)prog.rops.size();
+            blk.sub = sub;
+            blocks.push_back(std::move(blk));
+        }
+    };
+    auto group_entry = [&](const Table &tb, uint32_t regs) {
+        const dev::RegOp &r = tb.r;
+        const int le = __builtin_ctz((unsigned)elem_bytes);
+        dev::DiagTab d{};
+        d.octrl = r.octrl;
+        d.gplace = ~0u;
+        d.lane = 0xffffffu | ((uint32_t)r.a << 24);
+        d.wave = ~0u;
+        for (int q = 0; q < r.a; ++q) {
+            d.gpos |= (uint64_t)r.gt[q] << (8 * q);
+            d.gplace &= ~((15u ^ (uint32_t)(__builtin_ctz(r.gtb[q]) - le)) << (4 * q));
+        }
+        for (int t = 0; t < lane_bits; ++t)
+            if ((r.lane_ok >> t) & 1) d.lane &= ~((15u ^ (r.rd[t] - (uint32_t)le)) << (4 * t));
+        for (int t = 0; (1 << t) < nwaves; ++t)
+            if (r.wwave[1 << t])
+                d.wave &= ~((15u ^ (uint32_t)(__builtin_ctz(r.wwave[1 << t]) - le)) << (4 * t));
+        for (int j = 0, k = 0; j < rb; ++j)
+            if ((regs >> j) & 1) {
+                if ((tb.regs >> j) & 1) d.wave &= ~((15u ^ (uint32_t)tb.place[j]) << (12 + 4 * k));
+                ++k;
+            }
+        return d;
+    };
+    // A run of diagonal items commutes: tables with few register bits are
+    // gathered so that each group's register bits stay within two.
+    auto emit_tables = [&](int first, int last) {
+        struct Group {
+            uint32_t regs;
+            std::vector<Table *> tabs;
+        };
+        std::vector<Table> tabs;
+        for (int i = first; i < last; ++i) tabs.push_back(make_table(items[i]));
+        std::vector<Group> groups;
+        for (Table &tb : tabs) {
+            const bool few = __builtin_popcount(tb.regs) <= 2;
+            if (few) {
+                Group *to = nullptr;
+                for (Group &g : groups)
+                    if ((int)g.tabs.size() < dev::kDiagGroup && __builtin_popcount(g.regs | tb.regs) <= 2) {
+                        to = &g;
+                        break;
+                    }
+                if (!to) {
+                    groups.push_back({0, {}});
+                    to = &groups.back();
+                } else {
+                    ++saved;
+                }
+                to->regs |= tb.regs;
+                to->tabs.push_back(&tb);
+            }
+            if (few && group) continue;
+            put_blocks(tb, -1);
+            prog.rops.push_back(tb.r);
+            prog.flops_per_amp += 6.0;
+        }
+        if (!group) return;
+        for (Group &g : groups) {
+            dev::RegOp r{};
+            r.kind = dev::ROP_DGRP;
+            r.a = (int)g.tabs.size();
+            r.creg = g.regs;
+            for (size_t k = 0; k < g.tabs.size(); ++k) {
+                r.dt[k] = group_entry(*g.tabs[k], g.regs);
+                put_blocks(*g.tabs[k], (int)k);
+            }
+            prog.rops.push_back(r);
+            prog.flops_per_amp += 6.0 + 6.0 * (double)(g.tabs.size() << __builtin_popcount(g.regs)) / nr;
+        }
+    };
+
     for (int i = 0; i < n_items; ++i) {
         Item &it = items[i];
         if ((it.need & ~S) != 0) {
@@ -744,151 +924,71 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
             emit_remap(nw, split);
             S = Sn;
         }
+        if (it.kind == dev::ROP_DIAG) {
+            int j = i + 1;
+            while (j < n_items && items[j].kind == dev::ROP_DIAG) ++j;
+            emit_tables(i, j);
+            i = j - 1;
+            continue;
+        }
         dev::RegOp r{};
         r.kind = it.kind;
-        if (it.kind == dev::ROP_DIAG) {
-            // table bits: every qubit of the members except the controls that
-            // all of them share and that lie outside the tile
-            uint64_t common = ~0ull;
-            for (const Op &o : it.members) common &= o.ctrl;
-            const uint64_t octrl = common & ~tile_mask;
-            const uint64_t tq_mask = it.all & ~octrl;
-            // table bit order: the qubits on lane bits first, by lane bit, so
-            // that the 16 lanes a ds_read_b128 serves together (lane bits 0-3)
-            // read distinct 16-byte slots of one 256-byte bank row, or the
-            // same slot (a broadcast): no bank conflicts
-            int tq[dev::kRegDiagMax], kt = 0;
-            for (int t = 0; t < lane_bits; ++t)
-                for (int p = 0; p < 64; ++p)
-                    if (((tq_mask >> p) & 1) && li[p] >= 0 && slot_of(p) < 0 && thr_of(p) == t)
-                        tq[kt++] = p;
-            for (int p = 0; p < 64; ++p) {
-                if (!((tq_mask >> p) & 1)) continue;
-                const int t = li[p] >= 0 && slot_of(p) < 0 ? thr_of(p) : -1;
-                if (t < 0 || t >= lane_bits) tq[kt++] = p;
+        const Op &op = it.op;
+        const bool two = op.k == 2;
+        const int j0 = slot_of(op.t[0]), j1 = two ? slot_of(op.t[1]) : -1;
+        const bool swap01 = two && j1 < j0;
+        r.a = swap01 ? j1 : j0;
+        r.b = two ? (swap01 ? j0 : j1) : 0;
+        // controls: register bits, thread-id bits (lane and wave masks),
+        // and bits outside the tile
+        r.lane_ok = ~0ull;
+        r.wave_ok = ~0u;
+        for (int p = 0; p < 64; ++p) {
+            if (!((op.ctrl >> p) & 1)) continue;
+            if (li[p] < 0) {
+                r.octrl |= 1ull << p;
+                continue;
             }
-            r.octrl = octrl;
-            const uint32_t eb = (uint32_t)elem_bytes;
-            for (int j = 0; j < kt; ++j) {
-                const uint32_t wgt = eb << j;
-                if (li[tq[j]] < 0) {
-                    r.gt[r.a] = (uint32_t)tq[j];
-                    r.gtb[r.a] = wgt;
-                    r.a += 1;
-                    continue;
-                }
-                const int sj = slot_of(tq[j]);
-                if (sj >= 0) {
-                    for (int x = 0; x < nr; ++x)
-                        if ((x >> sj) & 1) r.wr[x] |= wgt;
-                } else {
-                    const int t = thr_of(tq[j]);
-                    if (t >= lane_bits)
-                        for (int w = 0; w < nwaves; ++w)
-                            if ((w >> (t - lane_bits)) & 1) r.wwave[w] |= wgt;
-                }
+            const int sj = slot_of(p);
+            if (sj >= 0) {
+                r.creg |= 1u << sj;
+                continue;
             }
-            // lane thread-id bit t that is table bit j: bit t of lane_ok set,
-            // rd[t] = the bit's place in the byte offset (j + log2 eb)
-            r.lane_ok = 0;
-            for (int j = 0; j < kt; ++j) {
-                const int t = li[tq[j]] >= 0 && slot_of(tq[j]) < 0 ? thr_of(tq[j]) : -1;
-                if (t >= 0 && t < lane_bits) {
-                    r.lane_ok |= 1ull << t;
-                    r.rd[t] = (uint32_t)(j + __builtin_ctz(eb));
-                }
-            }
-            ImgBlock tab;
-            int changed = 0;
-            for (uint32_t row = 0; row < (1u << kt); ++row) {
-                uint64_t bits = octrl;
-                for (int j = 0; j < kt; ++j)
-                    if ((row >> j) & 1) bits |= 1ull << tq[j];
-                cd v(1, 0);
-                for (const Op &o : it.members) {
-                    if ((bits & o.ctrl) != o.ctrl) continue;
-                    uint32_t rix = 0;
-                    for (int j = 0; j < o.k; ++j)
-                        if ((bits >> o.t[j]) & 1) rix |= 1u << j;
-                    v *= o.U[rix];
-                }
-                if (v != cd(1, 0)) ++changed;
-                put_complex(tab.bytes, v, elem_bytes);
-            }
-            tab.align = std::max<uint32_t>(16u, eb << kt);
-            tab.op = (int)prog.rops.size();
-            tab.table = true;
-            if (octrl) {
-                // tiles that fail the controls outside the tile read ones
-                ImgBlock ones;
-                for (uint32_t row = 0; row < (1u << kt); ++row) put_complex(ones.bytes, cd(1, 0), elem_bytes);
-                ones.align = tab.align;
-                ones.op = tab.op;
-                ones.table = true;
-                ones.ones = true;
-                blocks.push_back(std::move(ones));
-            }
-            blocks.push_back(std::move(tab));
-            prog.diag_ops += 1;
-            prog.flops_per_amp += 6.0;
-            (void)changed;
-        } else {
-            const Op &op = it.op;
-            const bool two = op.k == 2;
-            const int j0 = slot_of(op.t[0]), j1 = two ? slot_of(op.t[1]) : -1;
-            const bool swap01 = two && j1 < j0;
-            r.a = swap01 ? j1 : j0;
-            r.b = two ? (swap01 ? j0 : j1) : 0;
-            // controls: register bits, thread-id bits (lane and wave masks),
-            // and bits outside the tile
-            r.lane_ok = ~0ull;
-            r.wave_ok = ~0u;
-            for (int p = 0; p < 64; ++p) {
-                if (!((op.ctrl >> p) & 1)) continue;
-                if (li[p] < 0) {
-                    r.octrl |= 1ull << p;
-                    continue;
-                }
-                const int sj = slot_of(p);
-                if (sj >= 0) {
-                    r.creg |= 1u << sj;
-                    continue;
-                }
-                const int t = thr_of(p);
-                if (t < lane_bits) {
-                    uint64_t lm = 0;
-                    for (int l = 0; l < 64; ++l)
-                        if ((l >> t) & 1) lm |= 1ull << l;
-                    r.lane_ok &= lm;
-                } else {
-                    uint32_t wm = 0;
-                    for (int w = 0; w < nwaves; ++w)
-                        if ((w >> (t - lane_bits)) & 1) wm |= 1u << w;
-                    r.wave_ok &= wm;
-                }
-            }
-            auto sw = [](int x) { return ((x & 1) << 1) | ((x >> 1) & 1); };
-            const int D = 1 << op.k;
-            const double frac = 1.0 / (double)(1ull << popc(op.ctrl));
-            int e = 0;
-            if (it.kind == dev::ROP_R1 || it.kind == dev::ROP_R2) {
-                for (int row = 0; row < D; ++row)
-                    for (int col = 0; col < D; ++col)
-                        r.md[e++] = swap01 ? it.rm[(size_t)sw(row) * D + sw(col)]
-                                           : it.rm[(size_t)row * D + col];
-                prog.flops_per_amp += frac * (two ? 14.0 : 6.0);
+            const int t = thr_of(p);
+            if (t < lane_bits) {
+                uint64_t lm = 0;
+                for (int l = 0; l < 64; ++l)
+                    if ((l >> t) & 1) lm |= 1ull << l;
+                r.lane_ok &= lm;
             } else {
-                const std::vector<cd> U = dense_matrix(op);
-                for (int row = 0; row < D; ++row)
-                    for (int col = 0; col < D; ++col) {
-                        const cd v = swap01 ? U[(size_t)sw(row) * D + sw(col)] : U[(size_t)row * D + col];
-                        r.md[e++] = v.real();
-                        r.md[e++] = v.imag();
-                    }
-                prog.flops_per_amp += frac * (two ? 30.0 : 14.0);
+                uint32_t wm = 0;
+                for (int w = 0; w < nwaves; ++w)
+                    if ((w >> (t - lane_bits)) & 1) wm |= 1u << w;
+                r.wave_ok &= wm;
             }
-            for (int x = 0; x < 32; ++x) r.mf[x] = (float)r.md[x];
         }
+        auto sw = [](int x) { return ((x & 1) << 1) | ((x >> 1) & 1); };
+        const int D = 1 << op.k;
+        const double frac = 1.0 / (double)(1ull << popc(op.ctrl));
+        int e = 0;
+        if (it.kind == dev::ROP_R1 || it.kind == dev::ROP_R2) {
+            for (int row = 0; row < D; ++row)
+                for (int col = 0; col < D; ++col)
+                    r.md[e++] = swap01 ? it.rm[(size_t)sw(row) * D + sw(col)]
+                                       : it.rm[(size_t)row * D + col];
+            prog.flops_per_amp += frac * (two ? 14.0 : 6.0);
+        } else {
+            const std::vector<cd> U = dense_matrix(op);
+            for (int row = 0; row < D; ++row)
+                for (int col = 0; col < D; ++col) {
+                    const cd v = swap01 ? U[(size_t)sw(row) * D + sw(col)] : U[(size_t)row * D + col];
+                    r.md[e++] = v.real();
+                    r.md[e++] = v.imag();
+                }
+            prog.flops_per_amp += frac * (two ? 30.0 : 14.0);
+        }
+        for (int x = 0; x < 32; ++x) r.mf[x] = (float)r.md[x];
+        if (op.ctrl) r.kind += dev::ROP_CTRL;
         prog.rops.push_back(r);
     }
     // Stores leave from the final layout.  With some of the three lowest tile
@@ -990,7 +1090,10 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
     prog.img.assign(off, 0);
     for (const ImgBlock &blk : blocks) {
         std::memcpy(prog.img.data() + blk.off, blk.bytes.data(), blk.bytes.size());
-        if (blk.ones) prog.rops[blk.op].b = (int32_t)blk.off;
+        if (blk.sub >= 0) {
+            dev::DiagTab &d = prog.rops[blk.op].dt[blk.sub];
+            (blk.ones ? d.ones : d.off) = blk.off;
+        } else if (blk.ones) prog.rops[blk.op].b = (int32_t)blk.off;
         else if (blk.table) prog.rops[blk.op].mat = blk.off;
         else prog.rops[blk.op].lane_off = blk.off;
     }
@@ -1002,10 +1105,17 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
     // kRegImageMax sends the pass to the LDS-tile kernel.
     static const int caps[] = {dev::kRegDiagMax, 6, 4, 3, 2};
     uint32_t img = 0;
+    int used = 0;
     for (int cap : caps) {
-        img = lower(cap);
+        img = lower(used = cap, false);
         if (img <= dev::kRegImageSoft) break;
     }
+    // Groups of tables where they take out at least a quarter of the ops: the
+    // kernel's instance with groups is 3 % slower on every other op (30-qubit
+    // brick, whose tables hold mostly three or four register bits: 10.57 ms per
+    // pass with its few groups, 10.22 without), and a QFT's runs of tables with
+    // one or none halve their passes (27 qubits: 2.17 -> 1.52 ms).
+    if (img <= dev::kRegImageMax && saved * 4 >= (int)prog.rops.size()) img = lower(used, true);
     if (img > dev::kRegImageMax) {
         mats.resize(mats_mark);
         prog.rops.clear();
@@ -1130,6 +1240,39 @@ std::string emulate_reg_pass(const TileProgram &prog, int rb, const std::vector<
                 }
                 continue;
             }
+            if (op.kind == dev::ROP_DGRP) {
+                const int le = __builtin_ctz((unsigned)elem_bytes);
+                auto wgt = [&](uint32_t w, int f) {
+                    const uint32_t n = (w >> (4 * f)) & 15u;
+                    return n == 15u ? 0u : 1u << (n + (uint32_t)le);
+                };
+                if (op.a < 1 || op.a > dev::kDiagGroup || __builtin_popcount(op.creg) > 2) return "bad table group";
+                for (int k = 0; k < op.a; ++k) {
+                    const dev::DiagTab &d = op.dt[k];
+                    uint32_t s_idx = (base & d.octrl) == d.octrl ? d.off : d.ones;
+                    for (int q = 0; q < (int)(d.lane >> 24); ++q)
+                        if ((base >> ((d.gpos >> (8 * q)) & 255)) & 1) s_idx ^= wgt(d.gplace, q);
+                    for (int t = 0; t < nt; ++t) {
+                        uint32_t idx = s_idx;
+                        for (int b = 0; b < 6; ++b)
+                            if ((t >> b) & 1) idx ^= wgt(d.lane, b);
+                        for (int b = 0; b < tb - 6; ++b)
+                            if ((t >> (6 + b)) & 1) idx ^= wgt(d.wave, b);
+                        for (int i = 0; i < nr; ++i) {
+                            uint32_t x = idx;
+                            for (int j = 0, f = 3; j < rb; ++j)
+                                if ((op.creg >> j) & 1) {
+                                    if ((i >> j) & 1) x ^= wgt(d.wave, f);
+                                    ++f;
+                                }
+                            cd v;
+                            if (!rd_cplx(x, &v)) return "diag table read out of the image";
+                            amp[(size_t)t * nr + i] *= v;
+                        }
+                    }
+                }
+                continue;
+            }
             if (op.kind == dev::ROP_DIAG) {
                 uint32_t s_idx = (uint32_t)op.mat;
                 if ((base & op.octrl) != op.octrl) s_idx = (uint32_t)op.b;
@@ -1148,8 +1291,11 @@ std::string emulate_reg_pass(const TileProgram &prog, int rb, const std::vector<
                 }
                 continue;
             }
-            const bool two = op.kind == dev::ROP_G2 || op.kind == dev::ROP_R2;
-            const bool real = op.kind == dev::ROP_R1 || op.kind == dev::ROP_R2;
+            const int kind = op.kind & ~dev::ROP_CTRL;
+            const bool two = kind == dev::ROP_G2 || kind == dev::ROP_R2;
+            const bool real = kind == dev::ROP_R1 || kind == dev::ROP_R2;
+            if (op.kind == kind && (op.creg || op.octrl || ~op.lane_ok || ~op.wave_ok))
+                return "controls on an op without them";
             const int D = two ? 4 : 2;
             auto mval = [&](int x) { return elem_bytes == 16 ? op.md[x] : (double)op.mf[x]; };
             const int off[4] = {0, 1 << op.a, two ? (1 << op.b) : 0,

@@ -1,6 +1,7 @@
 // Lowering of planned passes to tile-kernel instruction lists.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -34,6 +35,12 @@ struct TileProgram {
     int diag_ops = 0;                   // DIAG ops of the register program
     int mfma_k = 0;                     // widest matrix-core op (LDS kernel)
     double flops_per_amp = 0.0;
+    int tables() const {                // table ops: 0 none, 1 DIAG, 2 DGRP too
+        int v = 0;
+        for (const dev::RegOp &r : rops)
+            v = std::max(v, r.kind == dev::ROP_DGRP ? 2 : r.kind == dev::ROP_DIAG ? 1 : 0);
+        return v;
+    }
 };
 
 // Lower pass `ps` for a register kernel with rb register bits (rb = 0: LDS
