@@ -66,6 +66,8 @@ struct TileArgs {
     int32_t mfma_k;       // LDS kernel: widest matrix-core op of the pass (0 = none)
     int32_t tables;       // register kernel: 0 without table ops, 1 with DIAG, 2 with DGRP too
                           // (the leanest instance of the kernel runs it)
+    int32_t zero_stays;   // register kernel: 1 if its coefficients are such that zeros stay
+                          // zeros (none infinite or large), so a tile of zeros is left alone
     uint32_t img_bytes;   // register kernel: bytes of the pass's LDS image (multiple of 16)
     int32_t store_sync;   // register kernel: 1 = workgroup barrier between the ops and the
                           // stores (the stores go where other threads loaded)

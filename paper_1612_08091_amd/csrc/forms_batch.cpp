@@ -204,6 +204,7 @@ qsv::dev::TileArgs reg_args(const qsv::TileProgram &pg, int n, int64_t img_off) 
     ta.rb = 4;
     ta.n_ops = (int32_t)pg.rops.size();
     ta.tables = pg.tables();
+    ta.zero_stays = pg.zero_stays ? 1 : 0;
     for (int b2 = 0; b2 < pg.m; ++b2) ta.spos[b2] = pg.spos[b2];
     return ta;
 }

@@ -530,6 +530,7 @@ qsv_status run_tile_passes(qsv_sim *s, const std::vector<Pass> &passes) {
         if (pg.reg) {
             ta.n_ops = (int)nr;
             ta.tables = pg.tables();
+            ta.zero_stays = pg.zero_stays ? 1 : 0;
             QSV_HIP(s, qsv::dev::launch_tile_reg(s->opt.dtype, s->d_state, ta, drops + ro, dmat,
                                                  dcount + pi, s->stream));
         } else {

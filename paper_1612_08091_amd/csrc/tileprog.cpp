@@ -8,6 +8,7 @@
 // rule applied to the RB register slots).  Diagonal operations run in any
 // layout; passes with wider operations run on the LDS-tile kernel.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -486,6 +487,12 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
     int saved = 0;   // ops that groups of tables take out (or would)
     auto lower = [&](int cap, bool group) -> uint32_t {
     saved = 0;
+    prog.zero_stays = true;
+    // coefficients of gates and channels are at most 1; what is larger or not
+    // finite runs on every amplitude (0 times infinity is not 0)
+    auto zero_stays = [&](double x) {
+        if (!(std::fabs(x) <= 2.0)) prog.zero_stays = false;
+    };
     mats.resize(mats_mark);
     prog.rops.clear();
     prog.img.clear();
@@ -786,6 +793,8 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
                 v *= o.U[rix];
             }
             if (v != cd(1, 0)) ++changed;
+            zero_stays(v.real());
+            zero_stays(v.imag());
             put_complex(tab.bytes, v, elem_bytes);
         }
         tab.align = std::max<uint32_t>(16u, eb << kt);
@@ -987,6 +996,7 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
                 }
             prog.flops_per_amp += frac * (two ? 30.0 : 14.0);
         }
+        for (int x = 0; x < e; ++x) zero_stays(r.md[x]);
         for (int x = 0; x < 32; ++x) r.mf[x] = (float)r.md[x];
         if (op.ctrl) r.kind += dev::ROP_CTRL;
         prog.rops.push_back(r);

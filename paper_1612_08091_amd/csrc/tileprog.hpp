@@ -33,6 +33,7 @@ struct TileProgram {
     int diag_merged = 0;                // diagonal ops folded into another
     int real_ops = 0;                   // register ops split into phases x real matrix
     int diag_ops = 0;                   // DIAG ops of the register program
+    bool zero_stays = false;            // amplitudes of a tile that are all 0 stay 0 (register program)
     int mfma_k = 0;                     // widest matrix-core op (LDS kernel)
     double flops_per_amp = 0.0;
     int tables() const {                // table ops: 0 none, 1 DIAG, 2 DGRP too
