@@ -163,10 +163,11 @@ qsv_status qsv_apply_diag(qsv_sim *sim, const double *d, int32_t k, const int32_
  * amplitude moves to the basis state holding table[x] in the register and
  * the same values elsewhere; the other amplitudes stay.  Flushes the queue,
  * then runs at once (a gather into a second state-sized device buffer that
- * the handle keeps, then a pointer swap, or a copy back into a borrowed
- * state).  EINVAL: w outside 1..26, unknown or repeated qubits, w + c above
- * the live qubits, NULL table, or a table that is not a permutation (checked
- * before anything runs); ENOMEM if the second buffer cannot be allocated. */
+ * the handle keeps, then a pointer swap or, into a borrowed state or under
+ * controls, a copy back of what moved).  EINVAL: w outside 1..26, unknown or
+ * repeated qubits, w + c above the live qubits, NULL table, or a table that is
+ * not a permutation (checked before anything runs); ENOMEM if the second
+ * buffer cannot be allocated. */
 qsv_status qsv_apply_math(qsv_sim *sim, int32_t w, const int32_t *qubits, const uint32_t *table,
                           int32_t c, const int32_t *controls);
 

@@ -19,6 +19,8 @@ struct MathArgs {
     int32_t w;
     int32_t shift;
     uint32_t pos[kMaxMathBits];
+    int32_t nc;             // controls
+    uint32_t cpos[64];      // their positions, ascending
 };
 
 // out[j] = in[src(j)]: for j with all control bits set, src(j) is j with the
@@ -27,6 +29,11 @@ struct MathArgs {
 // overlap.  dim = 2^n amplitudes of the state's complex type.
 hipError_t math_gather(int dtype, const void *in, void *out, uint64_t dim, const MathArgs &a,
                        const uint32_t *inv, hipStream_t s);
+
+// The same in place, through a buffer of dim >> nc amplitudes: only those with
+// all controls set are gathered, then put back.
+hipError_t math_in_place(int dtype, void *psi, void *buf, uint64_t dim, const MathArgs &a,
+                         const uint32_t *inv, hipStream_t s);
 
 }  // namespace dev
 }  // namespace qsv
