@@ -32,7 +32,7 @@ constexpr int kAdjChain = 4;            // rotations fused into one step
 //    op: fz, sl, nfree, ectrl), then apply
 //    U_j^dagger = cos(theta_j/2) + i sin(theta_j/2) P_j to both tiles.
 //    axis 1, 2, 3 = X, Y, Z; lslot is the rotation's accumulator within the
-//    launch, gslot its row in the partial array.
+//    launch.
 //  kind ADJ_PHASE: a diagonal op (MONO, k targets) whose targets all lie
 //    outside the tile: op.gt holds the targets' global positions, op.touch
 //    the rows that change, op.ectrl the controls outside the tile, and
@@ -50,7 +50,6 @@ struct AdjOp {
     int32_t nsub;
     int32_t axis[kAdjChain];
     int32_t lslot[kAdjChain];
-    int32_t gslot[kAdjChain];
     int32_t sub0;
     double c[kAdjChain];
     double s[kAdjChain];
@@ -58,29 +57,33 @@ struct AdjOp {
 
 // Sub-steps of a block, on block rows r = 0..7 (bit j of r = block bit j):
 //  SUB_ROT: rotation about `axis` on block bit j (as in a chain), on the
-//    pairs whose rows contain cmask; lslot / gslot as for chains.
+//    pairs whose rows contain cmask; lslot as for chains.
 //  SUB_U1: the 2x2 matrix at pool[mat] on block bit j, rows containing cmask.
-//  SUB_DIAG: row r multiplied by pool[mat + r] for the rows in `touch`.
+//  SUB_DIAG: row r multiplied by pool[mat + r].
 //  SUB_PHASE: a diagonal op with k targets outside the tile: row index
-//    r_out from the tile base's bits gt[0..k-1]; if r_out is in `touch`, the
+//    r_out from the tile base's bits gt (byte q: the q-th target); if r_out is in `touch`, the
 //    rows containing cmask are multiplied by pool[mat + r_out] (cmask = 0:
 //    the whole tile, recorded as a pending phase).
 //  All: skipped on tiles whose base lacks one of the ectrl bits.
 enum AdjSubKind { SUB_ROT = 0, SUB_U1 = 1, SUB_DIAG = 2, SUB_PHASE = 3 };
-struct AdjSub {
+// 64 bytes, one scalar load: a block reads its next sub-step while it runs one.
+struct alignas(64) AdjSub {
     int32_t kind;
     int32_t j;
-    int32_t cmask;
     int32_t axis;
+    int32_t cmask;
     int32_t lslot;
-    int32_t gslot;
     int32_t k;
     uint32_t touch;
-    uint32_t gt[6];
+    int32_t pad;
     uint64_t ectrl;
-    double c, s;
-    int64_t mat;
+    uint64_t gt;              // target positions, a byte each
+    union {
+        struct { double c, s; };
+        int64_t mat;
+    };
 };
+static_assert(sizeof(AdjSub) == 64, "one scalar load");
 
 constexpr int kAdjWaves = 4;            // waves per workgroup (256 threads)
 constexpr int kAdjMaxRot = 256;         // rotations per launch (LDS accumulators)
@@ -99,12 +102,14 @@ int adjoint_tile_grid(int dtype, int m, int mfma_k);
 // (widest matrix-core step of the sweep) as for the forward LDS tile
 // kernel; `ops` are ta.n_ops steps in order, holding at most kAdjMaxRot
 // rotations (lslot 0..nrot-1, each used once); `subs` the sub-steps of
-// their blocks; `pool` the matrices in the state's complex type.  Writes
-// partial[gslot * nb + 4 * block + wave] for every rotation of the pass,
-// nb = 4 * grid.
+// their blocks, with one entry more behind the last; `pool` the matrices in
+// the state's complex type; `rows[lslot]` the rotation's row in the partial
+// array.  Writes partial[row * nb + 4 * block + wave] for every rotation of
+// the pass, nb = 4 * grid.
 hipError_t adjoint_tile_pass(int dtype, void *psi, void *phi, const TileArgs &ta,
-                             const AdjOp *ops, const AdjSub *subs, const void *pool, int nrot,
-                             double *partial, int grid, hipStream_t s);
+                             const AdjOp *ops, const AdjSub *subs, const void *pool,
+                             const int32_t *rows, int nrot, double *partial, int grid,
+                             hipStream_t s);
 
 }  // namespace dev
 }  // namespace qsv

