@@ -154,6 +154,15 @@ qsv_status qsv_apply(qsv_sim *sim, const double *U, int32_t k, const int32_t *ta
 qsv_status qsv_apply_diag(qsv_sim *sim, const double *d, int32_t k, const int32_t *targets,
                           int32_t c, const int32_t *controls);
 
+/* Queue `count` items in order, as that many calls of qsv_apply (density 0), or
+ * of qsv_dm_apply and qsv_dm_apply_kraus (density 1): item i is head[3 i] = k,
+ * head[3 i + 1] = c, head[3 i + 2] = 0 for a gate or the number of Kraus
+ * matrices for a channel (density 1, c = 0).  Its k targets and c controls are
+ * the next entries of `qubits`, its matrices the next of `mats`.  Stops at the
+ * first item that fails, with that call's error; those before it stay queued. */
+qsv_status qsv_apply_list(qsv_sim *sim, int32_t density, int32_t count, const int32_t *head,
+                          const int32_t *qubits, const double *mats);
+
 /* Emulated math gate (Sec. 4.3.3: a BasicMathGate such as AddConstant applied
  * as the classical function it computes instead of its gate decomposition).
  * The register is qubits[0..w-1] (qubit ids, qubits[0] the least significant

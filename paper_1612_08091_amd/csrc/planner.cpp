@@ -165,6 +165,25 @@ struct Block {
     std::vector<int> members;
 };
 
+// The same for a diagonal op on a diagonal matrix.
+void scale_block(std::vector<cd> &M, const std::vector<int> &bq, const Op &op) {
+    const int kb = (int)bq.size(), dim = 1 << kb;
+    int lt[kMaxK];
+    uint32_t lctrl = 0;
+    for (int i = 0; i < kb; ++i) {
+        if ((op.ctrl >> bq[i]) & 1) lctrl |= 1u << i;
+        for (int j = 0; j < op.k; ++j)
+            if (op.t[j] == bq[i]) lt[j] = i;
+    }
+    for (uint32_t x = 0; x < (uint32_t)dim; ++x) {
+        if ((x & lctrl) != lctrl) continue;
+        int row = 0;
+        for (int j = 0; j < op.k; ++j) row |= (int)((x >> lt[j]) & 1u) << j;
+        cd &e = M[(size_t)x * dim + x];
+        e = op.U[row] * e;
+    }
+}
+
 Op build_block(const std::vector<Op> &ops, const Block &b) {
     if (b.members.size() == 1) return ops[b.members[0]];
     std::vector<int> bq;
@@ -176,7 +195,8 @@ Op build_block(const std::vector<Op> &ops, const Block &b) {
     for (int i = 0; i < dim; ++i) M[(size_t)i * dim + i] = 1;
     int norig = 0;
     for (int m : b.members) {
-        apply_op_to_block(M, bq, ops[m]);
+        if (b.diag) scale_block(M, bq, ops[m]);
+        else apply_op_to_block(M, bq, ops[m]);
         norig += ops[m].n_orig;
     }
     Gate g;
@@ -205,14 +225,23 @@ Op build_block(const std::vector<Op> &ops, const Block &b) {
 // kd_max: a diagonal op fuses with a diagonal block it shares a qubit with up
 // to kd_max qubits (a run of phases stays one diagonal op, cheap to apply);
 // every other block stays within k_max.
-std::vector<Op> fuse_impl(const std::vector<Op> &ops, int k_max, uint64_t allowed, int kd_max) {
+struct OpMasks {
+    uint64_t all, mix;
+    bool diag;
+};
+
+OpMasks masks_of(const Op &op) {
+    return {op.qubits(), op.mixing(), op.kind == Op::MONO && op.diag};
+}
+
+std::vector<Block> fuse_blocks(const std::vector<OpMasks> &ops, int k_max, uint64_t allowed,
+                               int kd_max) {
     std::vector<Block> blocks;
     std::vector<bool> frozen;   // blocks that may not absorb anything
     kd_max = std::max(kd_max, k_max);
     for (int i = 0; i < (int)ops.size(); ++i) {
-        const Op &op = ops[i];
-        const uint64_t all = op.qubits(), mix = op.mixing();
-        const bool dg = op.kind == Op::MONO && op.diag;
+        const uint64_t all = ops[i].all, mix = ops[i].mix;
+        const bool dg = ops[i].diag;
         const bool fusable =
             k_max >= 1 && (all & ~allowed) == 0 && popc(all) <= (dg ? kd_max : k_max);
         // latest block that does not commute with op
@@ -247,10 +276,26 @@ std::vector<Op> fuse_impl(const std::vector<Op> &ops, int k_max, uint64_t allowe
             frozen.push_back(!fusable);
         }
     }
+    return blocks;
+}
+
+std::vector<Op> fuse_impl(const std::vector<Op> &ops, int k_max, uint64_t allowed, int kd_max) {
+    std::vector<OpMasks> masks;
+    masks.reserve(ops.size());
+    for (const Op &op : ops) masks.push_back(masks_of(op));
+    const std::vector<Block> blocks = fuse_blocks(masks, k_max, allowed, kd_max);
     std::vector<Op> out;
     out.reserve(blocks.size());
     for (const Block &b : blocks) out.push_back(build_block(ops, b));
     return out;
+}
+
+// What plan_cost counts of a pass's fused ops: 1 for each that mixes, a quarter
+// for a diagonal one.
+double weight_of(const std::vector<Block> &blocks) {
+    double w = 0.0;
+    for (const Block &b : blocks) w += b.diag ? 0.25 : 1.0;
+    return w;
 }
 
 }  // namespace
@@ -304,7 +349,7 @@ std::vector<PlanGroup> plan_groups(const std::vector<PlanItem> &items, int n, in
 }
 
 std::vector<Pass> plan_passes(const std::vector<Op> &ops, int n, int m, int low_bits,
-                              int k_max, int kd_max) {
+                              int k_max, int kd_max, std::vector<double> *weights) {
     std::vector<PlanItem> items(ops.size());
     for (size_t i = 0; i < ops.size(); ++i) {
         items[i].need = items[i].mix = ops[i].mixing();
@@ -312,12 +357,18 @@ std::vector<Pass> plan_passes(const std::vector<Op> &ops, int n, int m, int low_
     }
     std::vector<Pass> passes;
     for (const PlanGroup &g : plan_groups(items, n, m, low_bits)) {
-        std::vector<Op> in_pass;
-        in_pass.reserve(g.idx.size());
-        for (int i : g.idx) in_pass.push_back(ops[i]);
         Pass ps;
         ps.tile = g.tile;
-        ps.ops = fuse_impl(in_pass, k_max, g.tile, kd_max);
+        if (weights) {
+            std::vector<OpMasks> masks;
+            for (int i : g.idx) masks.push_back(masks_of(ops[i]));
+            weights->push_back(weight_of(fuse_blocks(masks, k_max, g.tile, kd_max)));
+        } else {
+            std::vector<Op> in_pass;
+            in_pass.reserve(g.idx.size());
+            for (int i : g.idx) in_pass.push_back(ops[i]);
+            ps.ops = fuse_impl(in_pass, k_max, g.tile, kd_max);
+        }
         passes.push_back(std::move(ps));
     }
     return passes;
@@ -361,17 +412,20 @@ Op relabel_op(const Op &o, const int *pos) {
 
 std::vector<Pass> plan_passes_relabel(const std::vector<Op> &ops, int n, int m, int low_bits,
                                       int k_max, int kd_max, int page_bit, int page_cap,
-                                      int op_cap) {
+                                      int op_cap, std::vector<double> *weights) {
     std::vector<Pass> passes;
-    if (ops.empty() || n <= m) return plan_passes(ops, n, m, low_bits, k_max, kd_max);
+    if (ops.empty() || n <= m) return plan_passes(ops, n, m, low_bits, k_max, kd_max, weights);
     const int L = std::max(0, std::min(low_bits, m - kMaxK));
     constexpr int kNever = 1 << 30;
     int pos[64], at[64];            // qubit -> position, position -> qubit
     for (int q = 0; q < 64; ++q) pos[q] = at[q] = q;
     std::vector<uint64_t> need(ops.size()), all(ops.size());
+    std::vector<bool> diag(ops.size());
     for (size_t i = 0; i < ops.size(); ++i) {
-        need[i] = ops[i].mixing();
-        all[i] = ops[i].qubits();
+        const OpMasks o = masks_of(ops[i]);
+        need[i] = o.mix;
+        all[i] = o.all;
+        diag[i] = o.diag;
     }
     auto page_qubits = [&]() {
         uint64_t pm = 0;
@@ -381,8 +435,7 @@ std::vector<Pass> plan_passes_relabel(const std::vector<Op> &ops, int n, int m, 
     };
     auto to_positions = [&](uint64_t qmask) {
         uint64_t x = 0;
-        for (int q = 0; q < n; ++q)
-            if ((qmask >> q) & 1) x |= 1ull << pos[q];
+        for (; qmask; qmask &= qmask - 1) x |= 1ull << pos[__builtin_ctzll(qmask)];
         return x;
     };
     // Assign the qubits of `tile` (a mask of qubits) to the positions they
@@ -476,10 +529,17 @@ std::vector<Pass> plan_passes_relabel(const std::vector<Op> &ops, int n, int m, 
         for (int p = 0; p < n && popc(tile) < m; ++p) tile |= 1ull << at[p];
         Pass ps;
         ps.tile = to_positions(tile);
-        std::vector<Op> mapped;
-        mapped.reserve(in_pass.size());
-        for (int i : in_pass) mapped.push_back(relabel_op(ops[i], pos));
-        ps.ops = fuse_impl(mapped, k_max, ps.tile, kd_max);
+        if (weights) {
+            std::vector<OpMasks> masks;
+            masks.reserve(in_pass.size());
+            for (int i : in_pass) masks.push_back({to_positions(all[i]), to_positions(need[i]), diag[i]});
+            weights->push_back(weight_of(fuse_blocks(masks, k_max, ps.tile, kd_max)));
+        } else {
+            std::vector<Op> mapped;
+            mapped.reserve(in_pass.size());
+            for (int i : in_pass) mapped.push_back(relabel_op(ops[i], pos));
+            ps.ops = fuse_impl(mapped, k_max, ps.tile, kd_max);
+        }
         // next use of each tile qubit among the deferred ops
         int next[64];
         for (int q = 0; q < 64; ++q) next[q] = kNever;
@@ -541,6 +601,7 @@ std::vector<Pass> plan_passes_relabel(const std::vector<Op> &ops, int n, int m, 
         std::sort(order.begin(), order.end());
         move(ps, order, home);
         passes.push_back(std::move(ps));
+        if (weights) weights->push_back(0.0);
     }
     return passes;
 }
@@ -560,7 +621,8 @@ std::vector<Op> pass_ops_in_qubit_order(const std::vector<Pass> &passes, int n) 
     return out;
 }
 
-double plan_cost(const std::vector<Pass> &passes, int page_bit) {
+double plan_cost(const std::vector<Pass> &passes, const std::vector<double> &weights,
+                 int page_bit) {
     // relative time of a pass whose tile spans 2^h pages (measured on
     // 12-bit tiles of a 30-qubit complex128 state: flat up to 32 pages,
     // 1.2 x at 64, 2.3-4.7 x at 256), and of a pass that carries more fused
@@ -571,40 +633,42 @@ double plan_cost(const std::vector<Pass> &passes, int page_bit) {
     static const double kCost[11] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.05, 1.2, 1.6, 2.5, 3.5, 4.7};
     constexpr double kOpsPerPass = 16.0;
     double c = 0.0;
-    for (const Pass &p : passes) {
-        double w = 0.0;
-        for (const Op &o : p.ops) w += o.mixing() ? 1.0 : 0.25;
-        c += kCost[std::min(10, popc(page_bit >= 64 ? 0 : p.tile >> page_bit))] *
-             std::max(1.0, w / kOpsPerPass);
-    }
+    for (size_t i = 0; i < passes.size(); ++i)
+        c += kCost[std::min(10, popc(page_bit >= 64 ? 0 : passes[i].tile >> page_bit))] *
+             std::max(1.0, weights[i] / kOpsPerPass);
     return c;
 }
 
 std::vector<Pass> plan_tiled(const std::vector<Op> &ops, int n, int m, int k_max, int page_bit,
                              bool relabel) {
-    std::vector<Op> fused = fuse_impl(ops, k_max, ~0ull, kMaxK);
-    std::vector<Pass> best = plan_passes(fused, n, m, 3, k_max, kMaxK);
-    if (!relabel || n <= m) return best;
+    const std::vector<Op> fused = fuse_impl(ops, k_max, ~0ull, kMaxK);
+    if (!relabel || n <= m) return plan_passes(fused, n, m, 3, k_max, kMaxK);
     // the greedy grouping reacts to the caps unevenly: plan with several page
     // caps and caps on the ops a pass takes, and keep the cheapest plan
-    // (positions fixed included)
-    // The candidates are independent: large queues plan them on several host
-    // threads (the GPU waits for the plan), the choice is the same as in order.
+    // (positions fixed included).  The plans are compared by their tiles and the
+    // counts of their fused ops; only the one kept builds its matrices.
     struct Cand {
-        int op_cap, cap;
-        std::vector<Pass> plan;
+        int op_cap, cap;   // op_cap 0: the plan without relabeling
         double cost = 0.0;
     };
-    std::vector<Cand> cands;
+    std::vector<Cand> cands(1, Cand{0, 0, 0.0});
     for (int op_cap : {1 << 30, 40, 32})
-        for (int cap : {2, 3, 4, 5, 8}) cands.push_back({op_cap, cap, {}, 0.0});
-    auto work = [&](size_t i) {
-        cands[i].plan = plan_passes_relabel(fused, n, m, 3, k_max, kMaxK, page_bit, cands[i].cap,
-                                            cands[i].op_cap);
-        cands[i].cost = plan_cost(cands[i].plan, page_bit);
+        for (int cap : {2, 3, 4, 5, 8}) cands.push_back({op_cap, cap, 0.0});
+    auto make = [&](const Cand &c, std::vector<double> *weights) {
+        return c.op_cap ? plan_passes_relabel(fused, n, m, 3, k_max, kMaxK, page_bit, c.cap,
+                                              c.op_cap, weights)
+                        : plan_passes(fused, n, m, 3, k_max, kMaxK, weights);
     };
+    auto work = [&](size_t i) {
+        std::vector<double> weights;
+        const std::vector<Pass> plan = make(cands[i], &weights);
+        cands[i].cost = plan_cost(plan, weights, page_bit);
+    };
+    // The candidates are independent: large queues plan them on several host
+    // threads (a plan of 150 fused ops takes 20 us, a thread's start as long),
+    // the choice is the same as in order.
     const unsigned hw = std::thread::hardware_concurrency();
-    const size_t nth = fused.size() < 64 ? 1 : std::min<size_t>(cands.size(), std::min(8u, std::max(1u, hw)));
+    const size_t nth = fused.size() < 256 ? 1 : std::min<size_t>(cands.size(), std::min(8u, std::max(1u, hw)));
     if (nth <= 1) {
         for (size_t i = 0; i < cands.size(); ++i) work(i);
     } else {
@@ -617,12 +681,9 @@ std::vector<Pass> plan_tiled(const std::vector<Op> &ops, int n, int m, int k_max
             });
         for (std::thread &x : th) x.join();
     }
-    double best_cost = plan_cost(best, page_bit);
-    for (Cand &c : cands)
-        if (c.cost < best_cost - 1e-9) {
-            best_cost = c.cost;
-            best.swap(c.plan);
-        }
-    return best;
+    const Cand *best = &cands[0];
+    for (const Cand &c : cands)
+        if (c.cost < best->cost - 1e-9) best = &c;
+    return make(*best, nullptr);
 }
 }  // namespace qsv

@@ -1044,6 +1044,24 @@ qsv_status qsv_dm_apply_kraus(qsv_sim *s, int32_t nk, const double *kraus, int32
     return QSV_OK;
 }
 
+qsv_status qsv_apply_list(qsv_sim *s, int32_t density, int32_t count, const int32_t *head,
+                          const int32_t *qubits, const double *mats) {
+    QSV_CHECK(s);
+    if (count < 0 || (count > 0 && (!head || !qubits || !mats)))
+        return fail(s, QSV_EINVAL, "bad argument");
+    for (int i = 0; i < count; ++i) {
+        const int k = head[3 * i], c = head[3 * i + 1], nk = head[3 * i + 2];
+        if (k < 1 || k > qsv::kMaxK || c < 0 || nk < 0 || (nk > 0 && (!density || c > 0)))
+            return fail(s, QSV_EINVAL, "bad item in the list of gates");
+        QSV_TRY(nk > 0 ? qsv_dm_apply_kraus(s, nk, mats, k, qubits)
+                : density ? qsv_dm_apply(s, mats, k, qubits, c, qubits + k)
+                          : qsv_apply(s, mats, k, qubits, c, qubits + k));
+        qubits += k + c;
+        mats += (size_t)2 * std::max(nk, 1) << (2 * k);
+    }
+    return QSV_OK;
+}
+
 qsv_status qsv_dm_probabilities(qsv_sim *s, double *out) {
     QSV_CHECK(s);
     if (!out) return fail(s, QSV_EINVAL, "NULL argument");

@@ -104,8 +104,11 @@ std::vector<PlanGroup> plan_groups(const std::vector<PlanItem> &items, int n, in
 // across each other only when they commute.  Then each pass is fused to
 // k_max (only ops with all their qubits inside the tile are fused); runs of
 // diagonal ops fuse into diagonal ops of up to kd_max qubits (at least k_max).
+// weights: not built (the passes come without their ops); gets what plan_cost
+// counts of each pass instead.
 std::vector<Pass> plan_passes(const std::vector<Op> &ops, int n, int m, int low_bits,
-                              int k_max, int kd_max = 0);
+                              int k_max, int kd_max = 0,
+                              std::vector<double> *weights = nullptr);
 
 // The op with its qubit positions moved: position p -> pos[p] (controls and
 // targets; targets come out ascending, the matrix permuted to match).
@@ -122,7 +125,8 @@ Op relabel_op(const Op &o, const int *pos);
 // the identity, so the plan as a whole applies the ops and nothing else.
 std::vector<Pass> plan_passes_relabel(const std::vector<Op> &ops, int n, int m, int low_bits,
                                       int k_max, int kd_max, int page_bit, int page_cap,
-                                      int op_cap = 1 << 30);
+                                      int op_cap = 1 << 30,
+                                      std::vector<double> *weights = nullptr);
 
 // The ops of a plan in execution order, each on its qubits' own positions
 // (the positions in effect when no pass relabels).
@@ -132,14 +136,15 @@ std::vector<Op> pass_ops_in_qubit_order(const std::vector<Pass> &passes, int n);
 // number of 2 MiB pages its tile spans (a tile spread over 2^h pages reads
 // far slower once h passes about 5) and by its ops beyond what its memory
 // traffic hides (about 16 fused 2-qubit ops; a diagonal op counts a quarter).
-double plan_cost(const std::vector<Pass> &passes, int page_bit);
+double plan_cost(const std::vector<Pass> &passes, const std::vector<double> &weights,
+                 int page_bit);
 
 // Whole-queue fusion to k_max first (diagonal runs to kMaxK qubits), then
 // pass planning of the fused ops (blocks are not cut at pass boundaries);
 // three low bits stay in every tile for contiguous HBM runs.  relabel: also
 // plan with plan_passes_relabel under several page caps and caps on the ops
-// per pass (none, 40, 32) and keep the plan of least plan_cost (page_bit: the amplitude index bit of a 2 MiB page, 17 for
-// complex128 and 18 for complex64).
+// per pass (none, 40, 32) and keep the plan of least plan_cost (page_bit: the
+// amplitude index bit of a 2 MiB page, 17 for complex128 and 18 for complex64).
 std::vector<Pass> plan_tiled(const std::vector<Op> &ops, int n, int m, int k_max,
                              int page_bit = 64, bool relabel = false);
 

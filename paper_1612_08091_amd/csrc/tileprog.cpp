@@ -643,32 +643,20 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
                 if (!((B >> cur.thr[t]) & 1)) to.push_back(pos[cur.thr[t]]);
             for (size_t k = 0; k < from.size() && k < to.size(); ++k) fold[from[k]] = 1u << to[k];
         }
-        auto off = [&](uint32_t l) {
-            uint32_t h = 0;
-            for (int b = 0; b < m; ++b)
-                if (((l >> b) & 1) && pos[b] >= 0) h ^= (1u << pos[b]) ^ fold[b];
-            return h * (uint32_t)elem_bytes;
-        };
-        for (int i = 0; i < nr; ++i) {
-            uint32_t lo = 0, ln = 0;
-            for (int j = 0; j < rb; ++j)
-                if ((i >> j) & 1) {
-                    lo |= 1u << cur.reg[j];
-                    ln |= 1u << nw.reg[j];
-                }
-            r.wr[i] = off(lo);
-            r.rd[i] = off(ln);
+        uint32_t off[32];   // of the amplitude with one bit set; they combine by XOR
+        for (int b = 0; b < 32; ++b)
+            off[b] = pos[b] >= 0 ? ((1u << pos[b]) ^ fold[b]) * (uint32_t)elem_bytes : 0u;
+        r.wr[0] = r.rd[0] = 0;
+        for (int i = 1; i < nr; ++i) {
+            const int j = __builtin_ctz((unsigned)i), rest = i & (i - 1);
+            r.wr[i] = r.wr[rest] ^ off[cur.reg[j]];
+            r.rd[i] = r.rd[rest] ^ off[nw.reg[j]];
         }
-        uint32_t words[128];
-        for (int l = 0; l < 64; ++l) {
-            uint32_t w = 0, rd = 0;
-            for (int t = 0; t < lane_bits; ++t)
-                if ((l >> t) & 1) {
-                    w ^= off(1u << cur.thr[t]);
-                    rd ^= off(1u << nw.thr[t]);
-                }
-            words[l] = w;
-            words[64 + l] = rd;
+        uint32_t words[128] = {0};
+        for (int l = 1; l < 64; ++l) {
+            const int t = __builtin_ctz((unsigned)l), rest = l & (l - 1);
+            words[l] = words[rest] ^ (t < lane_bits ? off[cur.thr[t]] : 0u);
+            words[64 + l] = words[64 + rest] ^ (t < lane_bits ? off[nw.thr[t]] : 0u);
         }
         const uint32_t region = ((uint32_t)elem_bytes << (m - 1)) / (uint32_t)nwaves;
         for (int w = 0; w < nwaves; ++w) {
@@ -678,8 +666,8 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
             } else {
                 for (int t = lane_bits; t < tb; ++t)
                     if ((w >> (t - lane_bits)) & 1) {
-                        a ^= off(1u << cur.thr[t]);
-                        b ^= off(1u << nw.thr[t]);
+                        a ^= off[cur.thr[t]];
+                        b ^= off[nw.thr[t]];
                     }
             }
             r.wwave[w] = a;

@@ -90,6 +90,7 @@ _SIGS = {
     "qsv_deallocate": (ctypes.c_int, [_P, ctypes.c_int32]),
     "qsv_qubits": (ctypes.c_int, [_P, _P, _P]),
     "qsv_apply": (ctypes.c_int, [_P, _P, ctypes.c_int32, _P, ctypes.c_int32, _P]),
+    "qsv_apply_list": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.c_int32, _P, _P, _P]),
     "qsv_apply_diag": (ctypes.c_int, [_P, _P, ctypes.c_int32, _P, ctypes.c_int32, _P]),
     "qsv_apply_math": (ctypes.c_int, [_P, ctypes.c_int32, _P, _P, ctypes.c_int32, _P]),
     "qsv_dm_apply": (ctypes.c_int, [_P, _P, ctypes.c_int32, _P, ctypes.c_int32, _P]),
@@ -152,6 +153,68 @@ lib = _load()
 
 def _ptr(a: Optional[np.ndarray]):
     return None if a is None else ctypes.c_void_p(a.ctypes.data)
+
+
+def _ints(a) -> bytes:
+    """Qubit numbers as int32; bytes go to the library without the cost of an
+    array's address, which is most of the time of a call on a gate."""
+    return np.array(list(a) or [0], dtype=np.int32).tobytes()
+
+
+_COMPLEX = np.dtype(np.complex128)
+
+
+def _kraus_array(kraus) -> np.ndarray:
+    """The matrices of a channel as one array [K_j]."""
+    if isinstance(kraus, (list, tuple)) and len(kraus):
+        return np.array(kraus, dtype=np.complex128)
+    return np.stack([np.asarray(k, dtype=np.complex128) for k in kraus])
+
+
+class _GateList:
+    """Gates (and channels of a density matrix) for one qsv_apply_list call:
+    7 us of conversions and a library call per gate become 1."""
+
+    def __init__(self, one, density: bool):
+        self.one = one              # the handle's apply, for what the list cannot hold
+        self.density = density
+        self.clear()
+
+    def clear(self):
+        self.items, self.head, self.qubits, self.mats = [], [], [], []
+
+    def add(self, matrix, targets, controls, kraus=0):
+        """Adds an item; False (and nothing added) if its matrices do not have
+        the size that its targets ask for."""
+        u = matrix
+        if type(u) is not np.ndarray or u.dtype is not _COMPLEX:
+            u = np.asarray(u, dtype=np.complex128)
+        k = len(targets)
+        if not 1 <= k <= 5 or u.size != (kraus or 1) << 2 * k:
+            return False
+        self.items.append((matrix, targets, None if kraus else controls))
+        self.head += (k, len(controls), kraus)
+        self.qubits += targets
+        self.qubits += controls
+        self.mats.append(u.tobytes())
+        return True
+
+    def queue(self, handle):
+        """Queues what was added."""
+        if not self.items:
+            return
+        items = self.items
+        try:
+            head = np.array(self.head, dtype=np.int32).tobytes()
+            qubits = np.array(self.qubits, dtype=np.int32).tobytes()
+        except (TypeError, ValueError, OverflowError):
+            self.clear()
+            for it in items:        # the gate with that qubit raises
+                self.one(*it)
+            return
+        mats = b"".join(self.mats)
+        self.clear()
+        _check(lib.qsv_apply_list(handle, int(self.density), len(items), head, qubits, mats), handle)
 
 
 def _check(code: int, handle=None):
@@ -249,11 +312,9 @@ class Simulator:
 
     # -- gates ----------------------------------------------------------------
     def apply(self, matrix, targets: Sequence[int], controls: Sequence[int] = ()):
-        u = np.ascontiguousarray(matrix, dtype=np.complex128)
-        t = np.ascontiguousarray(list(targets) or [0], dtype=np.int32)
-        c = np.ascontiguousarray(list(controls) or [0], dtype=np.int32)
-        _check(lib.qsv_apply(self._h, _ptr(u), len(targets), _ptr(t), len(controls), _ptr(c)),
-               self._h)
+        u = np.asarray(matrix, dtype=np.complex128).tobytes()
+        _check(lib.qsv_apply(self._h, u, len(targets), _ints(targets), len(controls),
+                             _ints(controls)), self._h)
 
     def apply_diag(self, diag, targets: Sequence[int], controls: Sequence[int] = ()):
         """Queue diag(diag[0], ..., diag[2^k - 1]) on ``targets`` (bit j of the
@@ -281,8 +342,15 @@ class Simulator:
     def run(self, circuit, qubit_ids: Optional[Sequence[int]] = None):
         """Queue every gate of a circuit; circuit qubit j -> qubit_ids[j]."""
         ids = list(range(circuit.n)) if qubit_ids is None else list(qubit_ids)
-        for g in circuit.gates:
-            self.apply(g.matrix, [ids[q] for q in g.targets], [ids[q] for q in g.controls])
+        gates = _GateList(self.apply, False)
+        try:
+            for g in circuit.gates:
+                item = g.matrix, [ids[q] for q in g.targets], [ids[q] for q in g.controls]
+                if not gates.add(*item):
+                    gates.queue(self._h)
+                    self.apply(*item)
+        finally:
+            gates.queue(self._h)
 
     def flush(self):
         _check(lib.qsv_flush(self._h), self._h)
@@ -361,13 +429,13 @@ class Simulator:
         ``targets`` (k <= 2) by branch j, chosen with the uniform ``u`` from
         p_j = ||K_j psi||^2; the state becomes K_j psi / sqrt(p_j).  Returns
         (j, p) with p the array of branch probabilities."""
-        ks = np.ascontiguousarray(np.stack([np.asarray(k, dtype=np.complex128) for k in kraus]))
-        t = np.ascontiguousarray(list(targets), dtype=np.int32)
+        ks = _kraus_array(kraus)
+        t = list(targets)
         chosen = ctypes.c_int32(-1)
-        probs = np.zeros(len(ks), dtype=np.float64)
-        _check(lib.qsv_apply_kraus_sampled(self._h, len(ks), _ptr(ks), len(t), _ptr(t), float(u),
-                                           ctypes.byref(chosen), _ptr(probs)), self._h)
-        return int(chosen.value), probs
+        probs = (ctypes.c_double * len(ks))()
+        _check(lib.qsv_apply_kraus_sampled(self._h, len(ks), ks.tobytes(), len(t), _ints(t),
+                                           float(u), ctypes.byref(chosen), probs), self._h)
+        return int(chosen.value), np.frombuffer(probs, dtype=np.float64)
 
     def sample(self, u) -> np.ndarray:
         uu = np.ascontiguousarray(u, dtype=np.float64)
@@ -483,29 +551,34 @@ class FlatCircuit:
     def __init__(self, circuit, theta=None):
         gates = circuit.gates
         g = len(gates)
-        self.op = np.zeros(max(g, 1), dtype=np.int32)
-        self.k = np.zeros(max(g, 1), dtype=np.int32)
-        self.c = np.zeros(max(g, 1), dtype=np.int32)
-        self.qubits = np.zeros(max(g, 1) * 8, dtype=np.int32)
-        self.mat_off = np.zeros(max(g, 1), dtype=np.int64)
-        self.param = np.full(max(g, 1), -1, dtype=np.int32)
+        size = max(g, 1)
+        op, k, c = [OP_MATRIX] * size, [0] * size, [0] * size
+        qubits, mat_off, param = [0] * (8 * size), [0] * size, [-1] * size
         mats = []
         off = 0
         for i, gt in enumerate(gates):
-            qs = list(gt.targets) + list(gt.controls)
-            self.k[i] = len(gt.targets)
-            self.c[i] = len(gt.controls)
-            self.qubits[8 * i: 8 * i + len(qs)] = qs
+            qs = [*gt.targets, *gt.controls]
+            k[i] = len(gt.targets)
+            c[i] = len(gt.controls)
+            qubits[8 * i: 8 * i + len(qs)] = qs
             if gt.param >= 0:
-                self.op[i] = _AXIS_OP[gt.axis]
-                self.param[i] = gt.param
+                op[i] = _AXIS_OP[gt.axis]
+                param[i] = gt.param
             else:
-                self.op[i] = OP_MATRIX
-                self.mat_off[i] = off
-                mats.append(np.ascontiguousarray(gt.matrix, dtype=np.complex128).ravel())
-                off += gt.matrix.size
-        self.matrices = (np.concatenate(mats) if mats else np.zeros(1, np.complex128)).view(
-            np.float64).copy()
+                mat_off[i] = off
+                m = gt.matrix
+                off += m.size
+                mats.append(np.asarray(m, dtype=np.complex128).tobytes())
+        if len(qubits) != 8 * size:
+            raise ValueError("a gate on more than 8 qubits")
+        self.op = np.array(op, dtype=np.int32)
+        self.k = np.array(k, dtype=np.int32)
+        self.c = np.array(c, dtype=np.int32)
+        self.qubits = np.array(qubits, dtype=np.int32)
+        self.mat_off = np.array(mat_off, dtype=np.int64)
+        self.param = np.array(param, dtype=np.int32)
+        self.matrices = (np.frombuffer(b"".join(mats), dtype=np.float64).copy() if mats
+                         else np.zeros(2))
         th = circuit.theta if theta is None else theta
         self.params = np.ascontiguousarray(th if th is not None else np.zeros(1), dtype=np.float64)
         self.n_params = 0 if th is None else len(th)
@@ -552,11 +625,9 @@ class DensityMatrix:
         self.sim.close()
 
     def apply(self, matrix, targets: Sequence[int], controls: Sequence[int] = ()):
-        u = np.ascontiguousarray(matrix, dtype=np.complex128)
-        t = np.ascontiguousarray(list(targets) or [0], dtype=np.int32)
-        c = np.ascontiguousarray(list(controls) or [0], dtype=np.int32)
-        _check(lib.qsv_dm_apply(self.sim._h, _ptr(u), len(targets), _ptr(t), len(controls),
-                                _ptr(c)), self.sim._h)
+        u = np.asarray(matrix, dtype=np.complex128).tobytes()
+        _check(lib.qsv_dm_apply(self.sim._h, u, len(targets), _ints(targets), len(controls),
+                                _ints(controls)), self.sim._h)
 
     def channel(self, kraus, targets: Sequence[int]):
         ks = np.ascontiguousarray(np.stack([np.asarray(k, dtype=np.complex128) for k in kraus]))
@@ -566,11 +637,26 @@ class DensityMatrix:
 
     def run(self, events):
         """Queue ("gate", U, targets, controls) / ("kraus", [K_j], targets) events."""
-        for ev in events:
-            if ev[0] == "gate":
-                self.apply(ev[1], ev[2], ev[3])
+        def one(u, targets, controls):
+            if controls is None:
+                self.channel(u, targets)
             else:
-                self.channel(ev[1], ev[2])
+                self.apply(u, targets, controls)
+
+        gates = _GateList(one, True)
+        try:
+            for ev in events:
+                if ev[0] == "gate":
+                    item, kraus = (ev[1], list(ev[2]), list(ev[3])), 0
+                    held = gates.add(*item)
+                else:
+                    item = _kraus_array(ev[1]), list(ev[2]), None
+                    held = gates.add(item[0], item[1], (), len(item[0]))
+                if not held:
+                    gates.queue(self.sim._h)
+                    one(*item)
+        finally:
+            gates.queue(self.sim._h)
 
     def flush(self):
         self.sim.flush()
