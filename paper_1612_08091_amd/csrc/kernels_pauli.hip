@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "pauli.hpp"
+#include "result_store.hpp"
 
 namespace qsv {
 namespace dev {
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(1024) void k_pauli_total(const double *__restrict__
         v += (p[0] + p[1]) + (p[2] + p[3]);
     }
     v = group_sum<1024>(v, sh);
-    if (threadIdx.x == 0) *out = v;
+    if (threadIdx.x == 0) result_store(out, v);
 }
 
 template <typename R>

@@ -8,6 +8,7 @@
 #include <mutex>
 
 #include "device.hpp"
+#include "result_store.hpp"
 
 namespace qsv {
 namespace dev {
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(kRedThreads) void k_finish(const double *partial, i
         double acc = 0.0;
         for (int b = threadIdx.x; b < nblocks; b += blockDim.x) acc += partial[b * stride + j];
         acc = block_sum(acc, sh);
-        if (threadIdx.x == 0) out[j] = acc;
+        if (threadIdx.x == 0) result_store(out + j, acc);
     }
 }
 

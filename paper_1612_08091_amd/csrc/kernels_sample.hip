@@ -20,6 +20,7 @@
 #include <algorithm>
 
 #include "device.hpp"
+#include "result_store.hpp"
 
 namespace qsv {
 namespace dev {
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(kST) void k_sample(const typename VS<R>::T *__restr
         r = u[blockIdx.x] * top->total;
         const uint32_t c = first_above(cend, nc, 0.0, r, &found);
         if (c >= nc) {
-            if (tid == 0) out[blockIdx.x] = (uint64_t)(top->last < 0 ? 0 : top->last);
+            if (tid == 0) result_store(out + blockIdx.x, (uint64_t)(top->last < 0 ? 0 : top->last));
             return;
         }
         const uint64_t c0 = (uint64_t)c * kChunk;
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(kST) void k_sample(const typename VS<R>::T *__restr
         for (uint64_t b = blk; b-- > 0 && res < 0;) res = blast[b];
         for (uint64_t b = blk + 1; b < nb && res < 0; ++b) res = blast[b];
     }
-    out[blockIdx.x] = (uint64_t)(res < 0 ? 0 : res);
+    result_store(out + blockIdx.x, (uint64_t)(res < 0 ? 0 : res));
 }
 
 namespace {

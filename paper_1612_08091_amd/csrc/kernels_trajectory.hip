@@ -17,6 +17,7 @@
 #include <algorithm>
 
 #include "trajectory.hpp"
+#include "result_store.hpp"
 
 namespace qsv {
 namespace dev {
@@ -103,8 +104,14 @@ __global__ __launch_bounds__(kGT) void k_group_rdm(typename VG<R>::T *__restrict
     if (threadIdx.x < W) {
         double v = 0.0;
         for (int i = 0; i < kGT / 64; ++i) v += sh[i][threadIdx.x];
-        out[(size_t)blockIdx.x * W + threadIdx.x] = v;
+        result_store(out + (size_t)blockIdx.x * W + threadIdx.x, v);
     }
+}
+
+int group_blocks(const GroupArgs &a) {
+    const uint64_t ngroups = 1ull << (a.nq - a.k);
+    return (int)std::min<uint64_t>((ngroups + kGT - 1) / kGT,
+                                   std::min(1024, kGroupSums / group_width(a.kt)));
 }
 
 template <typename R, int K, int KT>
@@ -123,8 +130,7 @@ static hipError_t group_rdm_t(void *psi, const GroupArgs &a, double *out, int *b
         t.ur[e] = (R)a.ur[e];
         t.ui[e] = (R)a.ui[e];
     }
-    const unsigned nb = (unsigned)std::min<uint64_t>((t.ngroups + kGT - 1) / kGT,
-                                                      std::min(1024, kGroupSums / group_width(KT)));
+    const unsigned nb = (unsigned)group_blocks(a);
     *blocks = (int)nb;
     if (a.apply)
         hipLaunchKernelGGL((k_group_rdm<R, K, KT, true>), dim3(nb), dim3(kGT), 0, s, (T *)psi, t, out);

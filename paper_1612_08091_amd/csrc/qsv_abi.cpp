@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <atomic>
 #include <thread>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -209,6 +210,40 @@ qsv_status ensure_result(qsv_sim *s) {
 }
 
 double *result(qsv_sim *s) { return reinterpret_cast<double *>(s->h_res); }
+
+// Waits for results by their values: every word that the kernel will write is
+// set to kWaiting before the launch and looked at until it has changed, which
+// takes 6 us from launch to result where waiting for the stream takes 11.  The
+// results come from the stream's last kernel, so every kernel before it has
+// ended, and a word is written once that kernel has read what it depends on.
+// The kernels write their words with system scope.  After kPoll without a change
+// (a long kernel, a failed one, or a result that is this very NaN) the stream is
+// waited for as usual.
+constexpr uint64_t kWaiting = 0x7ff8a5c3d2e1f00dull;
+constexpr std::chrono::microseconds kPoll{500};
+
+void arm_results(qsv_sim *s, size_t first, size_t count) {
+    uint64_t *w = reinterpret_cast<uint64_t *>(s->h_res) + first;
+    std::fill(w, w + count, kWaiting);
+}
+
+qsv_status await_results(qsv_sim *s, size_t first, size_t count) {
+    const uint64_t *w = reinterpret_cast<const uint64_t *>(s->h_res) + first;
+    std::chrono::steady_clock::time_point start;
+    for (size_t i = 0, spins = 0; i < count;) {
+        if (__atomic_load_n(w + i, __ATOMIC_ACQUIRE) != kWaiting) {
+            ++i;
+            continue;
+        }
+        if (spins == 0) start = std::chrono::steady_clock::now();
+        __builtin_ia32_pause();
+        if ((++spins & 63) == 0 && std::chrono::steady_clock::now() - start > kPoll) {
+            QSV_HIP(s, hipStreamSynchronize(s->stream));
+            break;
+        }
+    }
+    return QSV_OK;
+}
 
 qsv_status materialize(qsv_sim *s) {
     if (s->invalid) return invalid_state(s);
@@ -697,11 +732,12 @@ qsv_status check_ids(qsv_sim *s, int32_t m, const int32_t *ids, uint64_t *mask_o
 
 qsv_status prob_split_host(qsv_sim *s, int pos, double *p0, double *p1) {
     QSV_TRY(ensure_ws(s, qsv::dev::reduce_workspace_bytes(s->n)));
+    arm_results(s, 0, 2);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::prob_split(s->opt.dtype, s->d_state, s->n, pos, (double *)s->d_ws,
                                     result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)s->dim() * s->elem());
-    QSV_TRY(sync(s));
+    QSV_TRY(await_results(s, 0, 2));
     *p0 = result(s)[0];
     *p1 = result(s)[1];
     s->stats.kernels += 2;
@@ -1216,13 +1252,14 @@ qsv_status qsv_get_probability(qsv_sim *s, int32_t m, const int32_t *qubits, con
     QSV_TRY(ensure_ws(s, qsv::dev::reduce_workspace_bytes(s->n)));
     qsv::dev::IndexArgs ia;
     index_args(mask, ones, ia);
+    arm_results(s, 0, 1);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::prob_masked(s->opt.dtype, s->d_state, 1ull << (s->n - m), ia,
                                      (double *)s->d_ws, result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)(1ull << (s->n - m)) * s->elem());
     s->stats.kernels += 2;
     s->stats.alg_bytes += (double)(1ull << (s->n - m)) * s->elem();
-    QSV_TRY(sync(s));
+    QSV_TRY(await_results(s, 0, 1));
     *out = *result(s);
     return QSV_OK;
 }
@@ -1286,11 +1323,12 @@ static qsv_status expectation_positions(qsv_sim *s, int nterms, const uint64_t *
     QSV_TRY(stage(s, blob.data(), blob.size(), &dblob));
     QSV_TRY(ensure_ws(s, p.partials() * sizeof(double)));
     const double bytes = (double)(p.sets.size() + p.wide.size()) * (double)s->dim() * s->elem();
+    arm_results(s, 0, 1);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::pauli_sum(s->opt.dtype, s->d_state, s->n, p, dblob, (double *)s->d_ws,
                                    result(s), s->stream));
     tend(s, tok, QSV_K_REDUCE, bytes);
-    QSV_TRY(sync(s));
+    QSV_TRY(await_results(s, 0, 1));
     s->stats.kernels += 1 + (p.sets.empty() ? 0 : 1) + (p.wide.empty() ? 0 : 1);
     s->stats.alg_bytes += bytes;
     *out = *result(s);
@@ -1422,6 +1460,8 @@ qsv_status qsv_apply_kraus_sampled(qsv_sim *s, int32_t nk, const double *kraus, 
     const double bytes = (ga.apply ? 2.0 : 1.0) * (double)s->dim() * s->elem();
     int blocks = 0;
     const int tok = tbegin(s);
+    const int width = qsv::dev::group_width(k);
+    arm_results(s, 0, (size_t)qsv::dev::group_blocks(ga) * width);
     QSV_HIP(s, qsv::dev::group_rdm(s->opt.dtype, s->d_state, ga, result(s), &blocks, s->stream));
     tend(s, tok, ga.apply ? QSV_K_DENSE : QSV_K_REDUCE, bytes);
     s->stats.kernels += 1;
@@ -1434,8 +1474,7 @@ qsv_status qsv_apply_kraus_sampled(qsv_sim *s, int32_t nk, const double *kraus, 
         s->stats.amp_gate_updates += (double)s->queue.size() * (double)s->dim();
         s->queue.clear();
     }
-    QSV_TRY(sync(s));
-    const int width = qsv::dev::group_width(k);
+    QSV_TRY(await_results(s, 0, (size_t)blocks * width));
     double h[16] = {0.0};
     for (int b = 0; b < blocks; ++b)
         for (int e = 0; e < width; ++e) h[e] += result(s)[(size_t)b * width + e];
@@ -1506,13 +1545,14 @@ qsv_status qsv_sample(qsv_sim *s, int32_t shots, const double *u, uint64_t *out)
     uint64_t *dout = reinterpret_cast<uint64_t *>(du + shots);
     if (direct) std::memcpy(du, u, ub);
     else QSV_HIP(s, hipMemcpyAsync(du, u, ub, hipMemcpyHostToDevice, s->stream));
+    if (direct) arm_results(s, (size_t)shots, (size_t)shots);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::sample(s->opt.dtype, s->d_state, s->n, shots, du, w, dout, s->stream));
     tend(s, tok, QSV_K_REDUCE, (double)s->dim() * s->elem());
     if (!direct) QSV_HIP(s, hipMemcpyAsync(out, dout, ub, hipMemcpyDeviceToHost, s->stream));
     s->stats.kernels += 3;
     s->stats.alg_bytes += (double)s->dim() * s->elem();
-    QSV_TRY(sync(s));
+    QSV_TRY(direct ? await_results(s, (size_t)shots, (size_t)shots) : sync(s));
     if (direct) std::memcpy(out, dout, ub);
     return QSV_OK;
 }

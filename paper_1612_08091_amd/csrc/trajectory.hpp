@@ -26,6 +26,8 @@ struct GroupArgs {
 // Doubles of a partial matrix: the diagonal, then re, im of rho[a][b], a < b,
 // ordered by b, then a.
 inline int group_width(int kt) { return kt == 1 ? 4 : 16; }
+// Workgroups of the pass.
+int group_blocks(const GroupArgs &a);
 // One pass over the state; every workgroup writes its partial matrix to
 // out[block * group_width(kt)] (host memory that the device writes), *blocks
 // of them.
