@@ -102,7 +102,8 @@ int adjoint_tile_grid(int dtype, int m, int mfma_k);
 // (widest matrix-core step of the sweep) as for the forward LDS tile
 // kernel; `ops` are ta.n_ops steps in order, holding at most kAdjMaxRot
 // rotations (lslot 0..nrot-1, each used once); `subs` the sub-steps of
-// their blocks, with one entry more behind the last; `pool` the matrices in
+// their blocks, with one entry more behind the last (this pass's are the
+// ta.img_bytes from ta.img_off on); `pool` the matrices in
 // the state's complex type; `rows[lslot]` the rotation's row in the partial
 // array.  Writes partial[row * nb + 4 * block + wave] for every rotation of
 // the pass, nb = 4 * grid.

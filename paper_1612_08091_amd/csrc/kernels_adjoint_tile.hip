@@ -530,10 +530,16 @@ __global__ __launch_bounds__(kNT) void k_adj_tile(typename VT<R>::T *__restrict_
     T *tf = tp + tsize;
     double *acc = reinterpret_cast<double *>(tf + tsize);
     const uint32_t tid = threadIdx.x;
+    Warm warm;
+    Warm warm_subs;
+    warm.ask<kNT>(ops, (uint32_t)ta.n_ops * (uint32_t)sizeof(AdjOp), tid);
+    warm_subs.ask<kNT>(reinterpret_cast<const unsigned char *>(subs) + ta.img_off, ta.img_bytes, tid);
     for (uint32_t i = tid; i < (uint32_t)(nrot * kAdjWaves); i += kNT) acc[i] = 0.0;
     const uint64_t dep_tid = deposit_bits(tid & (tsize - 1), ta.tpos, m);
     const uint32_t swz_tid = swz<R>(tid & (tsize - 1));
     const uint64_t n_tiles = ta.n_tiles;
+    warm.settle();
+    warm_subs.settle();
     for (uint64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         uint64_t base = t;
         for (int i = 0; i < m; ++i) {

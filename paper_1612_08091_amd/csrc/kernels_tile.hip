@@ -46,12 +46,15 @@ __global__ __launch_bounds__(kNT) void k_tile_lds(typename VT<R>::T *__restrict_
     const int m = ta.m;
     const uint32_t tsize = 1u << m;
     const uint32_t tid = threadIdx.x;
+    Warm warm;
+    warm.ask<kNT>(ops, (uint32_t)ta.n_ops * (uint32_t)sizeof(TileOp), tid);
     // this thread's share of every tile: local indices j + tid, j = 0, kNT, ...
     const uint64_t dep_tid = deposit_bits(tid & (tsize - 1), ta.tpos, m);
     const uint64_t dep_tid_f = deposit_bits(tid & (tsize - 1), ta.spos, m);
     const uint32_t swz_tid = swz<R>(tid & (tsize - 1));
     const uint32_t n_tiles = (uint32_t)ta.n_tiles;
     if (tid == 0) s_tile = atomicAdd(counter, 1u);
+    warm.settle();
     __syncthreads();
     uint32_t t = __builtin_amdgcn_readfirstlane(s_tile);
     while (t < n_tiles) {

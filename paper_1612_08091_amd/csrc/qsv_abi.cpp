@@ -1985,7 +1985,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
     const std::vector<qsv::PlanGroup> groups = qsv::plan_groups(items, n, m, 3);
     struct Launch {
         int group;
-        size_t first, count, row0;
+        size_t first, count, row0, sub0;
         int nrot;
     };
     // a step waiting in the open block
@@ -2014,7 +2014,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
         for (int p = 0; p < 64; ++p) li[p] = ((tile >> p) & 1) ? c++ : -1;
         // blocks of three tile bits take the one-target and diagonal steps
         const bool use_blocks = mt >= 3;
-        Launch L{gi, aops.size(), 0, rows.size(), 0};
+        Launch L{gi, aops.size(), 0, rows.size(), subs.size(), 0};
         int prev = -1;   // step index of the launch's last op if it is a chain
         bool bopen = false;
         uint32_t bbits = 0;
@@ -2138,7 +2138,7 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
             if (rot && L.nrot == qsv::dev::kAdjMaxRot) {
                 close_block();
                 launches.push_back(L);
-                L = Launch{gi, aops.size(), 0, rows.size(), 0};
+                L = Launch{gi, aops.size(), 0, rows.size(), subs.size(), 0};
                 prev = -1;
             }
             const Op &st = steps[i];
@@ -2251,7 +2251,9 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
         reinterpret_cast<const qsv::dev::AdjSub *>((const unsigned char *)dpool + a_bytes);
     const int32_t *drows = reinterpret_cast<const int32_t *>((const unsigned char *)dpool + a_bytes + u_bytes);
     const void *dmat = (const unsigned char *)dpool + a_bytes + u_bytes + r_bytes;
-    for (const Launch &L : launches) {
+    for (size_t li = 0; li < launches.size(); ++li) {
+        const Launch &L = launches[li];
+        const size_t sub_end = li + 1 < launches.size() ? launches[li + 1].sub0 : subs.size();
         const uint64_t tile = groups[L.group].tile;
         qsv::dev::TileArgs ta{};
         ta.m = popc(tile);
@@ -2263,6 +2265,8 @@ qsv_status adjoint_reverse_tiled(qsv_sim *s, const std::vector<Gate> &gates,
             if ((tile >> p) & 1) ta.tpos[c++] = (uint32_t)p;
         ta.n_tiles = 1ull << (n - ta.m);
         ta.mfma_k = mfma_k;
+        ta.img_off = (int64_t)(L.sub0 * sizeof(qsv::dev::AdjSub));
+        ta.img_bytes = (uint32_t)((sub_end - L.sub0) * sizeof(qsv::dev::AdjSub));
         for (int i = 0; i < 64 && (i << 8) < (1 << ta.m); ++i) {
             uint64_t d = 0;
             for (int b = 8; b < ta.m; ++b)

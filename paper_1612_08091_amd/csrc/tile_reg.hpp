@@ -566,6 +566,8 @@ __global__ __launch_bounds__(1 << TB) void k_tile_reg(typename VT<R>::T *__restr
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Warm warm;
+    warm.ask<1 << TB>(ops, (uint32_t)ta.n_ops * (uint32_t)sizeof(RegOp), tid);
     {
         const uint4 *src = reinterpret_cast<const uint4 *>(
             reinterpret_cast<const unsigned char *>(pool) + ta.img_off);
@@ -603,6 +605,7 @@ __global__ __launch_bounds__(1 << TB) void k_tile_reg(typename VT<R>::T *__restr
         words.claim[to] = atomicAdd(counter, 1u);
     };
     if (tid == 0) claim(0);
+    warm.settle();
     uint32_t slot = 0;
     for (;;) {
         __syncthreads();   // the claim (and, the first time, the image) is in LDS
@@ -717,6 +720,8 @@ __global__ __launch_bounds__(1 << TB, 3) void k_tile_reg_batch(typename VT<R>::T
             // every wave is past the previous tile (its remaps and table
             // reads) before the image is overwritten
             __syncthreads();
+            Warm warm;
+            warm.ask<1 << TB>(ops + sg.op_begin, (uint32_t)ta.n_ops * (uint32_t)sizeof(RegOp), tid);
             const uint4 *src = reinterpret_cast<const uint4 *>(pool + ta.img_off);
             uint4 *dst = reinterpret_cast<uint4 *>(limg);
             for (uint32_t e = tid; e < (ta.img_bytes >> 4); e += (1u << TB)) dst[e] = src[e];
@@ -728,6 +733,7 @@ __global__ __launch_bounds__(1 << TB, 3) void k_tile_reg_batch(typename VT<R>::T
                 gl |= on & ta.g_thr[t];
                 gs |= on & ta.g_thr_f[t];
             }
+            warm.settle();
             __syncthreads();
             cur = lo;
         }
