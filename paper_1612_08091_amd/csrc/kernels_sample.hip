@@ -200,10 +200,12 @@ __global__ __launch_bounds__(kST) void k_sample(const typename VS<R>::T *__restr
     __shared__ int64_t shl[kST / 64];
     __shared__ uint32_t found;
     const uint32_t tid = threadIdx.x;
+    // (from host memory: on its way while the state is read)
+    const double draw = u[blockIdx.x];
     double r = 0.0, from = 0.0;
     uint64_t blk = 0;
     if (!SMALL) {
-        r = u[blockIdx.x] * top->total;
+        r = draw * top->total;
         const uint32_t c = first_above(cend, nc, 0.0, r, &found);
         if (c >= nc) {
             if (tid == 0) result_store(out + blockIdx.x, (uint64_t)(top->last < 0 ? 0 : top->last));
@@ -235,7 +237,7 @@ __global__ __launch_bounds__(kST) void k_sample(const typename VS<R>::T *__restr
     }
     double total;
     double c = from + scan_before(seg, sh, &total);
-    if (SMALL) r = u[blockIdx.x] * total;
+    if (SMALL) r = draw * total;
     uint32_t hit = ~0u;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {

@@ -8,8 +8,8 @@
 // pinned host memory and the host, which decides the branch, adds them in
 // order: one kernel per channel and no copy.
 // Bound by HBM for large states (one read and one write), by the launch and the
-// host's wait for small ones: on 16 qubits 4.3 us (two qubits) and 9.6 (three),
-// about 25 us a channel with the host's part, against 53 as a tile pass, a
+// host's wait for small ones: on 16 qubits 4.3 us (two qubits) and 5.8 (three),
+// about 13 us a channel with the host's part, against 53 as a tile pass, a
 // reduction in two kernels and the upload of the pass.  (Workgroups of one wave
 // there take 4.1 us, but leave the host four times the sums: no gain.)
 #include <hip/hip_runtime.h>
@@ -42,6 +42,20 @@ __global__ __launch_bounds__(kGT) void k_group_rdm(typename VG<R>::T *__restrict
     using T = typename VG<R>::T;
     constexpr int D = 1 << K, DT = 1 << KT, W = KT == 1 ? 4 : 16;
     __shared__ double sh[kGT / 64][W];
+    // The matrix comes with the kernel's arguments, which lie in host memory:
+    // one load per thread and LDS, not a row of scalar loads that each cross to
+    // the host (three qubits, 16 in all: 9.7 -> 5.8 us).  From LDS it goes to
+    // registers for the whole loop: 256 of them for three qubits in complex128,
+    // and still the faster (27 qubits 849 -> 811 us, read in the loop 866; 24
+    // qubits 80.5 -> 82).
+    __shared__ T mat[APPLY ? D * D : 1];
+    if (APPLY) {
+        if (threadIdx.x < D * D) {
+            mat[threadIdx.x].x = a.ur[threadIdx.x];
+            mat[threadIdx.x].y = a.ui[threadIdx.x];
+        }
+        __syncthreads();
+    }
     double acc[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) acc[w] = 0.0;
@@ -63,7 +77,7 @@ __global__ __launch_bounds__(kGT) void k_group_rdm(typename VG<R>::T *__restrict
                 R yr = 0, yi = 0;
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    const R mr = a.ur[r * D + c], mi = a.ui[r * D + c];
+                    const R mr = mat[r * D + c].x, mi = mat[r * D + c].y;
                     yr += mr * x[c].x - mi * x[c].y;
                     yi += mr * x[c].y + mi * x[c].x;
                 }
