@@ -81,6 +81,8 @@ struct TileArgs {
     uint32_t spos[40];    // LDS kernel, stores: position of tile bit i (== tpos[i] unless
                           // the pass relabels its qubits)
     uint64_t dep_hi_f[64];// LDS kernel, stores: dep_hi over spos
+    uint32_t live;        // register kernel, if some: n_tiles counts the tiles whose numbers
+    int32_t some;         // have no bit outside `live`; the others hold zeros
 };
 
 // One operation of the register-resident tile kernel.

@@ -478,6 +478,14 @@ __device__ __forceinline__ uint64_t tile_base(uint32_t t, const TileArgs &ta) {
     return base;
 }
 
+// The t-th number, ascending, without a bit outside `live`.
+__device__ __forceinline__ uint32_t live_tile(uint32_t t, uint32_t live) {
+    uint32_t out = 0;
+    for (; t; t >>= 1, live &= live - 1)
+        if (t & 1u) out |= live & (0u - live);
+    return out;
+}
+
 // Issue the loads of tile t in the load layout (this thread's part gl of the
 // index).  The empty asms keep the per-register addresses and offsets from
 // being hoisted out of the tile loop (as 2^RB 64-bit values they would
@@ -609,8 +617,9 @@ __global__ __launch_bounds__(1 << TB) void k_tile_reg(typename VT<R>::T *__restr
     uint32_t slot = 0;
     for (;;) {
         __syncthreads();   // the claim (and, the first time, the image) is in LDS
-        const uint32_t tile = __builtin_amdgcn_readfirstlane(words.claim[slot]);
+        uint32_t tile = __builtin_amdgcn_readfirstlane(words.claim[slot]);
         if (tile >= n_tiles) break;
+        if (ta.some) tile = live_tile(tile, ta.live);
         slot ^= 1u;
         T amp[NR];
         load_tile<T, RB, m>(amp, psi, gl, tile, ta);
