@@ -6,10 +6,13 @@
 // gates and adds the targets' outer products, in double whatever the state's
 // dtype.  Hermitian, so 4 or 16 sums per thread.  The workgroups' sums go to
 // pinned host memory and the host, which decides the branch, adds them in
-// order: one kernel per channel and no copy.
+// order: one kernel per channel and no copy.  A call returns with the state in
+// memory for every stream.  Where the host watches the sums of a pass that also
+// writes the state, its workgroups therefore release them behind their waves'
+// stores (see kReleaseBlocks); else it waits for the stream.
 // Bound by HBM for large states (one read and one write), by the launch and the
 // host's wait for small ones: on 16 qubits 4.3 us (two qubits) and 5.8 (three),
-// about 13 us a channel with the host's part, against 53 as a tile pass, a
+// about 14 us a channel with the host's part, against 53 as a tile pass, a
 // reduction in two kernels and the upload of the pass.  (Workgroups of one wave
 // there take 4.1 us, but leave the host four times the sums: no gain.)
 #include <hip/hip_runtime.h>
@@ -38,7 +41,8 @@ struct GroupArgsT {
 
 template <typename R, int K, int KT, bool APPLY>
 __global__ __launch_bounds__(kGT) void k_group_rdm(typename VG<R>::T *__restrict__ psi,
-                                                   GroupArgsT<R, K> a, double *__restrict__ out) {
+                                                   GroupArgsT<R, K> a, double *__restrict__ out,
+                                                   bool release) {
     using T = typename VG<R>::T;
     constexpr int D = 1 << K, DT = 1 << KT, W = KT == 1 ? 4 : 16;
     __shared__ double sh[kGT / 64][W];
@@ -108,6 +112,7 @@ __global__ __launch_bounds__(kGT) void k_group_rdm(typename VG<R>::T *__restrict
         }
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (release) stores_arrived();
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         double v = acc[w];
@@ -118,7 +123,9 @@ __global__ __launch_bounds__(kGT) void k_group_rdm(typename VG<R>::T *__restrict
     if (threadIdx.x < W) {
         double v = 0.0;
         for (int i = 0; i < kGT / 64; ++i) v += sh[i][threadIdx.x];
-        result_store(out + (size_t)blockIdx.x * W + threadIdx.x, v);
+        double *p = out + (size_t)blockIdx.x * W + threadIdx.x;
+        if (release) result_release(p, v);
+        else result_store(p, v);
     }
 }
 
@@ -147,9 +154,11 @@ static hipError_t group_rdm_t(void *psi, const GroupArgs &a, double *out, int *b
     const unsigned nb = (unsigned)group_blocks(a);
     *blocks = (int)nb;
     if (a.apply)
-        hipLaunchKernelGGL((k_group_rdm<R, K, KT, true>), dim3(nb), dim3(kGT), 0, s, (T *)psi, t, out);
+        hipLaunchKernelGGL((k_group_rdm<R, K, KT, true>), dim3(nb), dim3(kGT), 0, s, (T *)psi, t, out,
+                           group_releases(a));
     else
-        hipLaunchKernelGGL((k_group_rdm<R, K, KT, false>), dim3(nb), dim3(kGT), 0, s, (T *)psi, t, out);
+        hipLaunchKernelGGL((k_group_rdm<R, K, KT, false>), dim3(nb), dim3(kGT), 0, s, (T *)psi, t, out,
+                           false);
     return hipGetLastError();
 }
 

@@ -1494,7 +1494,9 @@ qsv_status qsv_apply_kraus_sampled(qsv_sim *s, int32_t nk, const double *kraus, 
         s->stats.amp_gate_updates += (double)s->queue.size() * (double)s->dim();
         s->queue.clear();
     }
-    QSV_TRY(await_results(s, 0, (size_t)blocks * width));
+    // (a call returns with the state written)
+    QSV_TRY(ga.apply && !qsv::dev::group_releases(ga) ? sync(s)
+                                                      : await_results(s, 0, (size_t)blocks * width));
     double h[16] = {0.0};
     for (int b = 0; b < blocks; ++b)
         for (int e = 0; e < width; ++e) h[e] += result(s)[(size_t)b * width + e];

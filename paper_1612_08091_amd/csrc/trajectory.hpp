@@ -28,6 +28,14 @@ struct GroupArgs {
 inline int group_width(int kt) { return kt == 1 ? 4 : 16; }
 // Workgroups of the pass.
 int group_blocks(const GroupArgs &a);
+// With apply: whether the partial matrices are written behind the state's stores,
+// so that the host may watch them; if not, it has to wait for the stream, which
+// takes 4 us more.  Each workgroup that does so writes its XCD's L2 back: a step of
+// one gate on two qubits and one channel takes 15.1 us so on 14 qubits (16
+// workgroups) against 18.8 with the wait, 17.1 against 19.0 on 17 qubits (128), and
+// as long on 18 (256).
+constexpr int kReleaseBlocks = 128;
+inline bool group_releases(const GroupArgs &a) { return a.apply && group_blocks(a) <= kReleaseBlocks; }
 // One pass over the state; every workgroup writes its partial matrix to
 // out[block * group_width(kt)] (host memory that the device writes), *blocks
 // of them.
