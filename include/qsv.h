@@ -269,9 +269,10 @@ qsv_status qsv_get_expectation(qsv_sim *sim, int32_t nterms, const uint64_t *xma
                                const uint64_t *zmask, const double *coeff, double *out);
 
 /* As qsv_get_expectation, with the imaginary part of sum_t coeff[t] <P_t> in
- * *im_out.  A Pauli sum with real coefficients is Hermitian, so the
- * imaginary part is zero up to rounding; it is returned so that callers (and
- * the parity tests) can check that.  Flushes; synchronises. */
+ * *im_out.  A Pauli sum with real coefficients is Hermitian: amplitudes are
+ * taken in pairs whose imaginary parts cancel exactly, so it is 0, or NaN where
+ * a coefficient, or an amplitude under a string with X letters, is not finite.
+ * Flushes; synchronises. */
 qsv_status qsv_get_expectation_complex(qsv_sim *sim, int32_t nterms, const uint64_t *xmask,
                                        const uint64_t *zmask, const double *coeff, double *re_out,
                                        double *im_out);

@@ -1381,17 +1381,32 @@ qsv_status qsv_get_expectation_complex(qsv_sim *s, int32_t nterms, const uint64_
     // multiplies its string's value instead.
     std::vector<double> c(coeff, coeff + nterms);
     double odd = 0.0, one = 1.0;
+    *im_out = 0.0;
     for (int t = 0; t < nterms; ++t)
         if (!std::isfinite(c[t])) {
             double v = 0.0;
             QSV_TRY(expectation_positions(s, 1, &x[t], &z[t], &one, &v));
             odd += c[t] * v;
+            *im_out += c[t] * 0.0;
             c[t] = 0.0;
         }
     QSV_TRY(expectation_positions(s, nterms, x.data(), z.data(), c.data(), re_out));
     *re_out += odd;
-    // each pair's imaginary parts cancel; a state that is not finite shows
-    *im_out = *re_out - *re_out;
+    // Both members of a pair are summed, and their imaginary parts cancel exactly.
+    // What a state that is not finite leaves of them (0 times infinity) shows in
+    // the strings that have pairs, those with X letters.
+    if (!std::isfinite(*re_out)) {
+        std::vector<uint64_t> px, pz;
+        for (int t = 0; t < nterms; ++t)
+            if (x[t]) {
+                px.push_back(x[t]);
+                pz.push_back(z[t]);
+            }
+        const std::vector<double> ones(px.size(), 1.0);
+        double pairs = 0.0;
+        QSV_TRY(expectation_positions(s, (int)px.size(), px.data(), pz.data(), ones.data(), &pairs));
+        *im_out += pairs * 0.0;
+    }
     return QSV_OK;
 }
 
