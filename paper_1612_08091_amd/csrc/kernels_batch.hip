@@ -399,11 +399,12 @@ __global__ __launch_bounds__(kNT) void k_batch_pauli(const BatchSeg *__restrict_
                     local = __builtin_fma(q, sign_of(sreg >> u), local);
                 }
             }
-            // i^{ny} times the pair's 2 Re (ny even) or 2 i Im (odd); without X
+            // i^{ny} times the pair's 2 Re (ny even) or 2 i Im (odd; the 2 goes to
+            // the sum, the largest coefficients have no room for it); without X
             // letters, or where both members of every pair are summed, 1
             const int ny = tm.ny & 3;
-            double c = ny == 0 || ny == 3 ? tm.c : -tm.c;
-            if (far || xr) c *= 2.0;
+            const double c = ny == 0 || ny == 3 ? tm.c : -tm.c;
+            if (far || xr) local *= 2.0;
             const uint32_t s = (uint32_t)(__popcll(j0 & z) + __popc(tid & (uint32_t)z)) & 1u;
             acc = __builtin_fma(local, s ? -c : c, acc);
         }

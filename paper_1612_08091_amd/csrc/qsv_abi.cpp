@@ -1377,13 +1377,16 @@ qsv_status qsv_get_expectation_complex(qsv_sim *s, int32_t nterms, const uint64_
     }
     QSV_TRY(do_flush(s));
     QSV_TRY(materialize(s));
-    // The strings' coefficients go into one running sum; one that is not finite
-    // multiplies its string's value instead.
+    // The strings' coefficients go into one running sum, times the 2 of a pair and
+    // up to 8 of them added first; one that is not finite, or so large that this
+    // might overflow where its string's share does not, multiplies its string's
+    // value instead.
+    constexpr double kLarge = 0x1p1000;
     std::vector<double> c(coeff, coeff + nterms);
     double odd = 0.0, one = 1.0;
     *im_out = 0.0;
     for (int t = 0; t < nterms; ++t)
-        if (!std::isfinite(c[t])) {
+        if (!(std::fabs(c[t]) <= kLarge)) {
             double v = 0.0;
             QSV_TRY(expectation_positions(s, 1, &x[t], &z[t], &one, &v));
             odd += c[t] * v;
