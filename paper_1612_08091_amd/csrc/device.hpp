@@ -343,6 +343,18 @@ struct BatchLaunch {
     const void *reg_pool;         // LDS images
     uint32_t reg_img_max;
 };
+// The chip's XCDs; workgroup w runs on XCD w mod 8.
+constexpr unsigned kXcds = 8;
+// Work items of XCD x, a contiguous range: from xcd_first(items, x) up to the next.
+constexpr uint64_t xcd_first(uint64_t items, uint64_t x) { return items * x / kXcds; }
+// Workgroups for them, as many on every XCD: one for each item of the longest range,
+// at most as many as are resident.  (A grid rounded down to whole XCDs gave the
+// workgroups that had two items twice the time of the others: 13 circuits of 14 and
+// 15 qubits, 100 strings each, complex64: 217 us a run, now 161.)
+inline unsigned xcd_grid(uint64_t items, uint64_t resident) {
+    const uint64_t longest = (items + kXcds - 1) / kXcds, room = resident / kXcds;
+    return (unsigned)(kXcds * (longest < room ? longest : room > 0 ? room : 1));
+}
 inline int batch_chunk_log(int dtype) { return dtype == 0 ? 11 : 12; }
 hipError_t batch_launch(int dtype, const BatchLaunch &L, hipStream_t s);
 int batch_occupancy(int dtype, int mb, int mfma_k);   // resident workgroups per CU

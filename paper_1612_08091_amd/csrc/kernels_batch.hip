@@ -22,9 +22,6 @@ __constant__ uint32_t kIdentityPos[40] = {0,  1,  2,  3,  4,  5,  6,  7,  8,  9,
                                           14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27,
                                           28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39};
 
-// The chip's XCDs; workgroup w runs on XCD w mod 8.
-constexpr unsigned kXcds = 8;
-
 // +1 or -1 by bit 0 of s
 __device__ __forceinline__ double sign_of(uint32_t s) {
     return __hiloint2double((int)(0x3ff00000u | (s << 31)), 0);
@@ -333,8 +330,8 @@ __global__ __launch_bounds__(kNT) void k_batch_pauli(const BatchSeg *__restrict_
     __shared__ double sh[16];
     const uint32_t tid = threadIdx.x;
     const uint64_t xcd = blockIdx.x & (kXcds - 1), per = gridDim.x / kXcds;
-    const uint64_t it1 = items * (xcd + 1) / kXcds;
-    for (uint64_t it = items * xcd / kXcds + blockIdx.x / kXcds; it < it1; it += per) {
+    const uint64_t it1 = xcd_first(items, xcd + 1);
+    for (uint64_t it = xcd_first(items, xcd) + blockIdx.x / kXcds; it < it1; it += per) {
         const BatchSeg sg = segs[find_seg(segs, nseg, it)];
         const BatchCircuit bc = circuits[sg.circuit];
         const int cl = LOG < bc.n ? LOG : bc.n;
@@ -488,9 +485,7 @@ static hipError_t batch_t(const BatchLaunch &L, hipStream_t s) {
             hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
                 &occ, reinterpret_cast<const void *>(k_batch_pauli<R>), kNT, 0);
             if (e != hipSuccess) return e;
-            // whole rounds of the XCDs
-            const uint64_t most = (uint64_t)L.cus * std::max(1, occ);
-            const unsigned pg = (unsigned)(std::max<uint64_t>(1, std::min(items, most) / kXcds) * kXcds);
+            const unsigned pg = xcd_grid(items, (uint64_t)L.cus * std::max(1, occ));
             hipLaunchKernelGGL((k_batch_pauli<R>), dim3(pg), dim3(kNT), 0, s, L.segs + sb, ns, items,
                                L.circuits, L.terms, (const T *)L.states, L.partial);
             hipLaunchKernelGGL(k_batch_finish, dim3((ns + 3) / 4), dim3(256), 0, s, L.segs + sb, ns,
