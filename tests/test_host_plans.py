@@ -32,3 +32,7 @@ def run_check(tmp_path, name, *sources):
 
 def test_xcd_split(tmp_path):
     run_check(tmp_path, "xcd_split_check")
+
+
+def test_pauli_plan(tmp_path):
+    run_check(tmp_path, "pauli_plan_check", "pauli_plan.cpp")
