@@ -291,10 +291,33 @@ std::vector<Op> fuse_impl(const std::vector<Op> &ops, int k_max, uint64_t allowe
 }
 
 // What plan_cost counts of a pass's fused ops: 1 for each that mixes, a quarter
-// for a diagonal one.
-double weight_of(const std::vector<Block> &blocks) {
+// for a diagonal one.  A block of gates that mix may still be diagonal as a whole
+// (gates that cancel), so those in which several members mix are built to see.
+// There are few: the ops of a pass have been fused before.  op_of(i): the pass's op
+// i (on any positions).
+template <typename F> double weight_of(const std::vector<Block> &blocks, const F &op_of) {
     double w = 0.0;
-    for (const Block &b : blocks) w += b.diag ? 0.25 : 1.0;
+    for (const Block &b : blocks) {
+        bool mixes = !b.diag;
+        // one that mixes, between diagonal ones without zeros, mixes
+        int may_cancel = 0;
+        for (size_t m = 0; mixes && m < b.members.size(); ++m) {
+            const Op &o = op_of(b.members[m]);
+            may_cancel += o.mixing() || std::find(o.U.begin(), o.U.end(), cd(0, 0)) != o.U.end();
+        }
+        if (may_cancel > 1) {
+            std::vector<Op> ops;
+            Block own;
+            own.diag = false;
+            for (int m : b.members) {
+                own.members.push_back((int)ops.size());
+                ops.push_back(op_of(m));
+                own.all |= ops.back().qubits();
+            }
+            mixes = build_block(ops, own).mixing() != 0;
+        }
+        w += mixes ? 1.0 : 0.25;
+    }
     return w;
 }
 
@@ -362,7 +385,8 @@ std::vector<Pass> plan_passes(const std::vector<Op> &ops, int n, int m, int low_
         if (weights) {
             std::vector<OpMasks> masks;
             for (int i : g.idx) masks.push_back(masks_of(ops[i]));
-            weights->push_back(weight_of(fuse_blocks(masks, k_max, g.tile, kd_max)));
+            weights->push_back(weight_of(fuse_blocks(masks, k_max, g.tile, kd_max),
+                                         [&](int i) -> const Op & { return ops[g.idx[i]]; }));
         } else {
             std::vector<Op> in_pass;
             in_pass.reserve(g.idx.size());
@@ -533,7 +557,8 @@ std::vector<Pass> plan_passes_relabel(const std::vector<Op> &ops, int n, int m, 
             std::vector<OpMasks> masks;
             masks.reserve(in_pass.size());
             for (int i : in_pass) masks.push_back({to_positions(all[i]), to_positions(need[i]), diag[i]});
-            weights->push_back(weight_of(fuse_blocks(masks, k_max, ps.tile, kd_max)));
+            weights->push_back(weight_of(fuse_blocks(masks, k_max, ps.tile, kd_max),
+                                         [&](int i) -> const Op & { return ops[in_pass[i]]; }));
         } else {
             std::vector<Op> mapped;
             mapped.reserve(in_pass.size());

@@ -36,3 +36,7 @@ def test_xcd_split(tmp_path):
 
 def test_pauli_plan(tmp_path):
     run_check(tmp_path, "pauli_plan_check", "pauli_plan.cpp")
+
+
+def test_plan_weights(tmp_path):
+    run_check(tmp_path, "plan_weights_check", "planner.cpp")
