@@ -1227,9 +1227,14 @@ qsv_status qsv_apply_math(qsv_sim *s, int32_t w, const int32_t *qubits, const ui
     // borrowed one is worked on in place where there are controls (27 qubits,
     // one control: 814 + 853 us for gather and copy back, 448 + 357 in place),
     // and an own one from two controls, all above the bits of a 128-byte line
-    // (4 / 2^c of the state moved instead of 2).
+    // (4 / 2^c of the state moved instead of 2), where it is large enough to pay for
+    // a second kernel: a gate among others takes 17 us by the one route and 21 by
+    // the other up to 16 MiB, 18.2 and 20.3 with 32 MiB, 25 and 21 with 64 MiB, 95
+    // and 43 with 256 MiB.
+    constexpr uint64_t kInPlaceBytes = 64ull << 20;
     const uint64_t line = 128 / s->elem() - 1;
-    const bool part = s->owns_state ? a.nc >= 2 && !(ctrl & line) : a.nc >= 1;
+    const bool part = s->owns_state ? a.nc >= 2 && !(ctrl & line) && s->dim() * s->elem() >= kInPlaceBytes
+                                    : a.nc >= 1;
     const int tok = tbegin(s);
     if (part) {
         QSV_HIP(s, qsv::dev::math_in_place(s->opt.dtype, s->d_state, s->d_alt, s->dim(), a,
