@@ -60,6 +60,7 @@ struct qsv_sim {
     size_t ws_bytes = 0;
     unsigned char *h_res = nullptr;    // pinned: small inputs and results of the reductions, read
                                        // and written by their kernels directly
+    void *h_block = nullptr;           // the pinned block that holds it: a slot's first, or its own
     // op pool for tile passes: pinned host staging + device copy, two slots
     struct Slot {
         void *h = nullptr;
@@ -199,13 +200,24 @@ qsv_status invalid_state(qsv_sim *s) {
 
 // Pinned memory in which a reduction's last kernel leaves its result, so that
 // the host waits for that kernel and for no copy; sampling keeps its uniforms
-// and indices there too, up to kDirectShots of them.
+// and indices there too, up to kDirectShots of them.  It lies behind the first
+// upload slot, which most handles have by their first reduction (a block of its
+// own costs a new handle 12 us, and 12 to free); a handle that has uploaded nothing
+// gets one at its first reduction.
 constexpr size_t kDirectShots = 4096;
 constexpr size_t kResultBytes = 16 * kDirectShots;
 static_assert(kResultBytes >= sizeof(double) * qsv::dev::kGroupSums, "partial matrices");
 
+qsv_status pinned(qsv_sim *s, size_t bytes, void **out) {
+    QSV_HIP(s, hipHostMalloc(out, bytes, hipHostMallocDefault));
+    if (log_level() >= 2) std::fprintf(stderr, "qsv: pinned block of %zu bytes\n", bytes);
+    return QSV_OK;
+}
+
 qsv_status ensure_result(qsv_sim *s) {
-    if (!s->h_res) QSV_HIP(s, hipHostMalloc((void **)&s->h_res, kResultBytes, hipHostMallocDefault));
+    if (s->h_res) return QSV_OK;
+    QSV_TRY(pinned(s, kResultBytes, &s->h_block));
+    s->h_res = static_cast<unsigned char *>(s->h_block);
     return QSV_OK;
 }
 
@@ -250,7 +262,6 @@ qsv_status materialize(qsv_sim *s) {
     if (s->materialized) return QSV_OK;
     QSV_TRY(ensure_capacity(s, s->n));
     QSV_HIP(s, qsv::dev::fill_basis0(s->opt.dtype, s->d_state, s->dim(), s->stream));
-    QSV_TRY(ensure_result(s));
     s->materialized = true;
     return QSV_OK;
 }
@@ -281,11 +292,16 @@ qsv_status stage(qsv_sim *s, const void *data, size_t bytes, void **dptr) {
     }
     if (bytes > sl.bytes) {
         QSV_HIP(s, hipStreamSynchronize(s->stream));
-        if (sl.h) QSV_HIP(s, hipHostFree(sl.h));
+        if (sl.h && sl.h != s->h_block) QSV_HIP(s, hipHostFree(sl.h));
         if (sl.d) QSV_HIP(s, hipFree(sl.d));
         sl.h = sl.d = nullptr;
-        size_t b = std::max<size_t>(bytes, 1 << 20);
-        QSV_HIP(s, hipHostMalloc(&sl.h, b, hipHostMallocDefault));
+        sl.bytes = 0;
+        const size_t b = (std::max<size_t>(bytes, 1 << 20) + 255) & ~size_t(255);
+        QSV_TRY(pinned(s, b + (s->h_res ? 0 : kResultBytes), &sl.h));
+        if (!s->h_res) {
+            s->h_block = sl.h;
+            s->h_res = static_cast<unsigned char *>(sl.h) + b;
+        }
         QSV_HIP(s, hipMalloc(&sl.d, b));
         sl.bytes = b;
         if (!sl.done) QSV_HIP(s, hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
@@ -752,6 +768,7 @@ qsv_status check_ids(qsv_sim *s, int32_t m, const int32_t *ids, uint64_t *mask_o
 
 qsv_status prob_split_host(qsv_sim *s, int pos, double *p0, double *p1) {
     QSV_TRY(ensure_ws(s, qsv::dev::reduce_workspace_bytes(s->n)));
+    QSV_TRY(ensure_result(s));
     arm_results(s, 0, 2);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::prob_split(s->opt.dtype, s->d_state, s->n, pos, (double *)s->d_ws,
@@ -883,9 +900,9 @@ qsv_status qsv_destroy(qsv_sim *s) {
     if (s->owns_state && s->d_state) (void)hipFree(s->d_state);
     if (s->d_ws) (void)hipFree(s->d_ws);
     if (s->d_alt) (void)hipFree(s->d_alt);
-    if (s->h_res) (void)hipHostFree(s->h_res);
+    if (s->h_block) (void)hipHostFree(s->h_block);
     for (auto &sl : s->slot) {
-        if (sl.h) (void)hipHostFree(sl.h);
+        if (sl.h && sl.h != s->h_block) (void)hipHostFree(sl.h);
         if (sl.d) (void)hipFree(sl.d);
         if (sl.done) (void)hipEventDestroy(sl.done);
     }
@@ -1277,6 +1294,7 @@ qsv_status qsv_get_probability(qsv_sim *s, int32_t m, const int32_t *qubits, con
     QSV_TRY(ensure_ws(s, qsv::dev::reduce_workspace_bytes(s->n)));
     qsv::dev::IndexArgs ia;
     index_args(mask, ones, ia);
+    QSV_TRY(ensure_result(s));
     arm_results(s, 0, 1);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::prob_masked(s->opt.dtype, s->d_state, 1ull << (s->n - m), ia,
@@ -1348,6 +1366,7 @@ static qsv_status expectation_positions(qsv_sim *s, int nterms, const uint64_t *
     QSV_TRY(stage(s, blob.data(), blob.size(), &dblob));
     QSV_TRY(ensure_ws(s, p.partials() * sizeof(double)));
     const double bytes = (double)(p.sets.size() + p.wide.size()) * (double)s->dim() * s->elem();
+    QSV_TRY(ensure_result(s));
     arm_results(s, 0, 1);
     const int tok = tbegin(s);
     QSV_HIP(s, qsv::dev::pauli_sum(s->opt.dtype, s->d_state, s->n, p, dblob, (double *)s->d_ws,
@@ -1446,6 +1465,7 @@ qsv_status qsv_measure(qsv_sim *s, int32_t m, const int32_t *qubits, const doubl
         a.u[j] = u[j];
     }
     QSV_TRY(ensure_ws(s, qsv::dev::measure_workspace_bytes()));
+    QSV_TRY(ensure_result(s));
     auto *br = reinterpret_cast<qsv::dev::MeasureBranch *>(s->h_res);
     br->status = 1;
     int launches = 0;
@@ -1498,6 +1518,7 @@ qsv_status qsv_apply_kraus_sampled(qsv_sim *s, int32_t nk, const double *kraus, 
     if (!s->invalid && s->opt.mode == QSV_MODE_TILED) group_queue(s, ga);
     if (!ga.apply) QSV_TRY(do_flush(s));
     QSV_TRY(materialize(s));
+    QSV_TRY(ensure_result(s));
     ga.nq = s->n;
     if (ga.apply) QSV_TRY(launch_gate(s));
     const double bytes = (ga.apply ? 2.0 : 1.0) * (double)s->dim() * s->elem();
@@ -1585,6 +1606,7 @@ qsv_status qsv_sample(qsv_sim *s, int32_t shots, const double *u, uint64_t *out)
     const size_t ub = (size_t)shots * 8;
     const bool direct = (size_t)shots <= kDirectShots;
     QSV_TRY(ensure_ws(s, wsb + (direct ? 0 : 2 * ub)));
+    QSV_TRY(ensure_result(s));
     unsigned char *w = (unsigned char *)s->d_ws;
     double *du = direct ? result(s) : (double *)(w + wsb);
     uint64_t *dout = reinterpret_cast<uint64_t *>(du + shots);
@@ -1619,7 +1641,6 @@ qsv_status qsv_set_state(qsv_sim *s, const void *src, int32_t src_is_device) {
     s->queue.clear();
     s->invalid = false;
     QSV_TRY(ensure_capacity(s, s->n));
-    QSV_TRY(ensure_result(s));
     QSV_HIP(s, hipMemcpyAsync(s->d_state, src, s->dim() * s->elem(),
                               src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                               s->stream));
@@ -2367,7 +2388,6 @@ extern "C" qsv_status qsv_adjoint_gradient(qsv_sim *s, const qsv_circuit *circ,
     }
     const uint64_t dim = 1ull << n;
     QSV_TRY(ensure_vectors(s, dim));
-    QSV_TRY(ensure_result(s));
     void *psi = s->d_vec[0], *phi = s->d_vec[1];
     // partial sums per rotation: nb per workgroup-wave of the tiled sweep
     // (mode TILED), else per workgroup of the per-gate reverse kernels
@@ -2432,6 +2452,7 @@ extern "C" qsv_status qsv_adjoint_gradient(qsv_sim *s, const qsv_circuit *circ,
                                    (const uint64_t *)(w + off_z), (const double *)(w + off_c),
                                    (const int32_t *)(w + off_ny), s->stream));
     double *partial = (double *)(w + off_pa);
+    QSV_TRY(ensure_result(s));
     QSV_HIP(s, qsv::dev::dot_re(s->opt.dtype, psi, phi, dim, partial + (size_t)nb * nrot,
                                 result(s), s->stream));
     // reverse sweep
