@@ -107,7 +107,10 @@ typedef struct qsv_stats {
     uint64_t fused_ops;     /* operations after fusion */
     uint64_t passes;        /* HBM passes over the state (kernel launches on it) */
     uint64_t kernels;       /* all kernels launched */
-    double alg_bytes;       /* algorithmic HBM bytes of those launches */
+    double alg_bytes;       /* algorithmic HBM bytes of those launches: a tile pass reads and
+                               writes every tile that it visits (the first flush of a state
+                               leaves out tiles known to hold zeros; zeros that a kernel finds
+                               by reading are counted in full, though not written) */
     double alg_flops;       /* algorithmic floating-point operations */
     double amp_gate_updates;/* sum over original gates of 2^n */
 } qsv_stats;

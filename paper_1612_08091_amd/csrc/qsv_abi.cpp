@@ -606,8 +606,9 @@ qsv_status run_tile_passes(qsv_sim *s, const std::vector<Pass> &passes, uint64_t
             QSV_HIP(s, qsv::dev::launch_tile_pass(s->opt.dtype, s->d_state, ta, dlops + lo, dmat,
                                                   dcount + pi, s->stream));
         }
-        tend(s, tok, QSV_K_TILE, 2.0 * (double)s->dim() * s->elem());
-        account(s, (double)s->dim(), pg.flops_per_amp);
+        const double visited = (double)(ta.n_tiles << pg.m);
+        tend(s, tok, QSV_K_TILE, 2.0 * visited * s->elem());
+        account(s, visited, pg.flops_per_amp);
         if (log_level() >= 2)
             std::fprintf(stderr,
                          "qsv: pass %zu tile=%#llx m=%d %s ops=%zu remaps=%d real=%d diag=%d "
