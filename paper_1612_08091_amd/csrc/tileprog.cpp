@@ -1247,20 +1247,36 @@ std::string emulate_reg_pass(const TileProgram &prog, int rb, const std::vector<
                 if (op.a < 1 || op.a > dev::kDiagGroup || __builtin_popcount(op.creg) > 2) return "bad table group";
                 for (int k = 0; k < op.a; ++k) {
                     const dev::DiagTab &d = op.dt[k];
+                    // The kernel ORs the parts into the table's offset: each has a
+                    // place of its own, and the table lies at a multiple of its size.
+                    uint32_t used = 0;
+                    bool own = true;
+                    auto place = [&](uint32_t w, int f) {
+                        const uint32_t v = wgt(w, f);
+                        own = own && !(used & v);
+                        used |= v;
+                    };
+                    for (int q = 0; q < (int)(d.lane >> 24); ++q) place(d.gplace, q);
+                    for (int b = 0; b < 6; ++b) place(d.lane, b);
+                    for (int b = 0; b < tb - 6; ++b) place(d.wave, b);
+                    for (int f = 0; f < __builtin_popcount(op.creg); ++f) place(d.wave, 3 + f);
+                    uint32_t size = (uint32_t)elem_bytes;
+                    while (size <= used) size <<= 1;
+                    if (!own || d.off % size || (d.octrl && d.ones % size)) return "parts of a table's offset overlap";
                     uint32_t s_idx = (base & d.octrl) == d.octrl ? d.off : d.ones;
                     for (int q = 0; q < (int)(d.lane >> 24); ++q)
-                        if ((base >> ((d.gpos >> (8 * q)) & 255)) & 1) s_idx ^= wgt(d.gplace, q);
+                        if ((base >> ((d.gpos >> (8 * q)) & 255)) & 1) s_idx |= wgt(d.gplace, q);
                     for (int t = 0; t < nt; ++t) {
                         uint32_t idx = s_idx;
                         for (int b = 0; b < 6; ++b)
-                            if ((t >> b) & 1) idx ^= wgt(d.lane, b);
+                            if ((t >> b) & 1) idx |= wgt(d.lane, b);
                         for (int b = 0; b < tb - 6; ++b)
-                            if ((t >> (6 + b)) & 1) idx ^= wgt(d.wave, b);
+                            if ((t >> (6 + b)) & 1) idx |= wgt(d.wave, b);
                         for (int i = 0; i < nr; ++i) {
                             uint32_t x = idx;
                             for (int j = 0, f = 3; j < rb; ++j)
                                 if ((op.creg >> j) & 1) {
-                                    if ((i >> j) & 1) x ^= wgt(d.wave, f);
+                                    if ((i >> j) & 1) x |= wgt(d.wave, f);
                                     ++f;
                                 }
                             cd v;

@@ -40,3 +40,7 @@ def test_pauli_plan(tmp_path):
 
 def test_plan_weights(tmp_path):
     run_check(tmp_path, "plan_weights_check", "planner.cpp")
+
+
+def test_table_groups(tmp_path):
+    run_check(tmp_path, "table_groups_check", "planner.cpp", "tileprog.cpp")
