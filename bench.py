@@ -54,6 +54,7 @@ TRAFFIC_SOURCES = ("paper_1612_08091_amd/csrc/kernels_tile.hip",
                    "paper_1612_08091_amd/csrc/tileprog.hpp",
                    "paper_1612_08091_amd/csrc/planner.cpp",
                    "paper_1612_08091_amd/csrc/qsv_internal.hpp",
+                   "paper_1612_08091_amd/csrc/qsv_abi.cpp",
                    "paper_1612_08091_amd/build.py")
 
 
