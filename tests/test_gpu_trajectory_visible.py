@@ -43,6 +43,7 @@ def test_state_is_written_when_the_call_returns(n, dtype, tol):
         want = apply(psi, u, qubits)
         sim.reset()
         sim.state_pointer()
+        torch.cuda.synchronize()        # the reset has filled the buffer
         buf.copy_(psi)
         torch.cuda.synchronize()
         sim.apply(u, qubits)
