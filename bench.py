@@ -34,17 +34,18 @@ HBM_PEAK = 8.0e12          # MI355X HBM3E, bytes/s
 FP64_PEAK = 78.6e12        # MI355X FP64 (vector and matrix), flop/s
 
 # Measured HBM traffic of the dominant kernel (k_tile_reg<double,4,8,*>: the
-# instance with table ops, 123 of 132 launches in the profiled run, and the
-# one without, the 9 passes that only move qubits back; tiles of zeros, in a
+# instance with table ops, 82 of the 88 launches of two timed steps, and the
+# one without, the 6 passes that only move qubits back; tiles of zeros, in a
 # step's first passes, are read and not written), from two rocprofv3
 # --pmc runs of this script's main leg (FETCH_SIZE, then WRITE_SIZE, KiB per
-# dispatch, mean over the tile dispatches).  The counters are scaled by what
+# dispatch, mean over the tile dispatches of the timed steps; the warmup's first
+# flush visits fewer tiles).  The counters are scaled by what
 # they read for the copy probe of the same runs (16 GiB read + 16 GiB
 # written: FETCH_SIZE reads half the bytes, WRITE_SIZE all of them).  Valid
 # only for the sources they were taken with: the digest below covers every
 # file that shapes the kernel or its launches.
-TRAFFIC = {"kernel": "k_tile_reg<double,4,8,*>", "fetch_kib": 8421236.5, "write_kib": 14243408.5,
-           "fetch_scale": 2.0, "write_scale": 1.0, "digest": "9fdb76b222fb783a"}
+TRAFFIC = {"kernel": "k_tile_reg<double,4,8,*>", "fetch_kib": 8420378.6, "write_kib": 14243407.4,
+           "fetch_scale": 2.0, "write_scale": 1.0, "digest": "f1c4b7199c9a82fc"}
 TRAFFIC_SOURCES = ("paper_1612_08091_amd/csrc/kernels_tile.hip",
                    "paper_1612_08091_amd/csrc/kernels_tile_reg_f64.hip",
                    "paper_1612_08091_amd/csrc/tile_reg.hpp",

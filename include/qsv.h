@@ -32,6 +32,12 @@
  *   - A handle is not thread-safe; distinct handles are independent.  Device
  *     work runs asynchronously on the handle's HIP stream; faults from it are
  *     reported as QSV_EDEVICE by the next call that synchronises.
+ *   - "Synchronises" means: when the call returns, everything enqueued on the
+ *     handle before has run, and what it wrote to the state is in memory for
+ *     every stream.  Calls that return a few numbers (probabilities, Pauli sums,
+ *     samples, channel steps) wait for those and not for the stream, so their
+ *     last kernel, which has then read what it reads, may still be ending; a
+ *     fault that does not keep it from its result is left to the next call.
  *   - Ownership: callers own every array they pass; the library copies what it
  *     keeps.  The library owns its device buffers, except a borrowed state
  *     buffer (qsv_options.state), which the caller must keep alive until

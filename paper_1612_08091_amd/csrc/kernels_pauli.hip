@@ -4,17 +4,17 @@
 // k_pauli_tiles: strings whose X letters lie within one tile shape share its
 // reads of the state.  A workgroup of 512 threads takes tiles of 2^12
 // amplitudes: 8 per thread in registers, and the tile in LDS (64 or 32 KiB),
-// from which a thread reads the partners psi_{j^x} of its own.  A string then costs, per pair, one LDS read,
-// the one product its parity needs (mul, fma) and a signed add: the sign splits
-// into the tile's, the register's (uniform) and the thread's, and the
-// coefficient goes in with the thread's sign, so that one running sum serves
-// every string.  The next tile's amplitudes are on their way meanwhile.  With
-// 12 bits of tile a sum of 200 random strings of weight <= 4 on 25 qubits (111
-// X masks) reads the state 8 times: 1.73 ms in complex128, 2.5 TB/s, of which
-// the reads alone would take 0.7; the rest is the latency of 14 groups a tile
-// (21 vector and about 50 scalar instructions each) at four waves per SIMD.  As
-// one sweep per X mask it took 11.8 ms.  8 strings on 30 qubits: 2 reads, 5.7 ms
-// (6.0 TB/s), against 24.7.
+// from which a thread reads the partners psi_{j^x} of its own.  A string then
+// costs, per pair, one LDS read, the one product its parity needs (mul, fma) and a
+// signed add: the sign splits into the tile's, the register's (uniform) and the
+// thread's, and the coefficient goes in with the thread's sign, so that one running
+// sum serves every string.  The next tile's amplitudes are on their way meanwhile.
+// With 12 bits of tile a sum of 200 random strings of weight <= 4 on 25 qubits (111
+// X masks) reads the state 8 times: 1.6 ms in complex128, 2.7 TB/s, of which the
+// reads alone would take 0.7; the rest is the latency of 14 groups a tile (21 vector
+// and about 50 scalar instructions each) at four waves per SIMD.  As one sweep per X
+// mask it took 11.8 ms.  On 30 qubits 8 strings that two shapes hold take 2 reads,
+// 5.7 ms (6.0 TB/s; 24.7 as sweeps), 8 that one shape holds 2.9.
 // k_pauli_wide: the strings that fit in no tile, one sweep per X mask.
 #include <hip/hip_runtime.h>
 

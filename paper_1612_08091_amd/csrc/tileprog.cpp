@@ -488,8 +488,9 @@ void compile_pass(const Pass &ps, int rb, std::vector<double> &mats, TileProgram
     auto lower = [&](int cap, bool group) -> uint32_t {
     saved = 0;
     prog.zero_stays = true;
-    // coefficients of gates and channels are at most 1; what is larger or not
-    // finite runs on every amplitude (0 times infinity is not 0)
+    // coefficients of gates and channels are usually at most 1 (a trajectory's
+    // branches K / sqrt(p) may be larger); anything above 2 or not finite runs on
+    // every amplitude (0 times infinity is not 0)
     auto zero_stays = [&](double x) {
         if (!(std::fabs(x) <= 2.0)) prog.zero_stays = false;
     };
