@@ -50,7 +50,7 @@ int main() {
                     static const int caps[] = {2, 4, 8}, op_caps[] = {1 << 30, 32};
                     return setting == 0 ? plan_passes(ops, n, m, 3, k_max, kMaxK, weights)
                            : setting == 7
-                               ? plan_passes_relabel(ops, n, m, 3, k_max, kMaxK, 64, 8, 40, weights)
+                               ? plan_passes_relabel(ops, n, m, 3, k_max, kMaxK, 17, 8, 40, weights)
                                : plan_passes_relabel(ops, n, m, 3, k_max, kMaxK, 9, caps[setting % 3],
                                                      op_caps[setting % 2], weights);
                 };
